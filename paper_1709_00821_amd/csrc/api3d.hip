@@ -16,6 +16,7 @@
 
 #include "../../include/fdtd_plasma3d.h"
 #include "internal3d.h"
+#include "slabs3d.h"
 
 using namespace fdtdp;
 
@@ -41,8 +42,6 @@ int fail3(int code, const char *fmt, ...)
             return fail3(FDTD_E_DEVICE, "%s failed: %s", #expr, hipGetErrorString(e_));    \
     } while (0)
 
-constexpr int kSlabSteps = 16;     // steps taken on a slab before the next
-constexpr int64_t kSlabAbove = 192LL << 20, kSlabBytes = 100LL << 20, kSlabMin = 24;
 constexpr int64_t kGraphNodes = 1 << 16;   // launches of a run that are captured at most
 constexpr int64_t kAlign3 = 256;
 constexpr int kAuxMargin = 8;      // incident grid spans z in [tf_lo - 8, tf_hi + 8]
@@ -200,15 +199,8 @@ int plan3(const fdtd3d_desc *d, Plan3 &pl, bool keep_tables)
     // (4, and 3 where those are less than two rounds of the waves that fit: 96^3 66 -> 60 us a step)
     const int64_t waves = (nz + 63) / 64 * d->ny * ((d->nx + 3) / 4);
     pl.ni = d->x_planes ? d->x_planes : pl.exec == FDTD3D_EXEC_FUSED ? 32 : waves < 8192 ? 3 : 4;
-    // A grid that does not fit the 256 MB memory-side cache is stepped in slabs
-    // of planes that do, kSlabSteps steps on each before the next (a periodic x
-    // has no first slab).  Around 100 MB of fields a slab: 256^3 FP64 849 -> 774
-    // us a step, 384^3 FP32 1297 -> 1185, where 200 MB gain 1% and 50 MB cost as much in launches.
-    const int64_t plane = 6 * d->ny * nz * pl.esize;
-    if (pl.exec == FDTD3D_EXEC_SPLIT && !d->periodic_x && d->nx * plane > kSlabAbove) {
-        const int64_t L = std::max<int64_t>(kSlabMin, kSlabBytes / plane), n = (d->nx + L - 1) / L;
-        if (n > 1) pl.slabp = up3((d->nx + n - 1) / n, pl.ni);
-    }
+    // slabs (a periodic x has no first one)
+    if (pl.exec == FDTD3D_EXEC_SPLIT && !d->periodic_x) pl.slabp = slab_planes(d->nx, 6 * d->ny * nz * pl.esize, pl.ni);
     Layout3 L;
     const int es = pl.esize;
     const int copies = pl.exec == FDTD3D_EXEC_FUSED ? 2 : 1;
@@ -478,9 +470,7 @@ int split_step(fdtd3d *h, int pend)
     return pts ? h->slot : -1;
 }
 
-// n steps of it slab by slab: step t of a slab covers the planes t below the
-// slab's, so that every H finds the E of the plane above it one step behind and
-// every E the H of the plane below already advanced.
+// n <= kSlabSteps steps of it slab by slab (slabs3d.h).
 template <typename T>
 void slab_steps(fdtd3d *h, int n)
 {
@@ -495,8 +485,9 @@ void slab_steps(fdtd3d *h, int n)
     for (int64_t s = 0; s < nx; s += L)
         for (int t = 0; t < n; ++t) {
             Geo3 g = h->geo;
-            g.ia = std::max<int64_t>(s - t, 0);
-            g.ib = s + L < nx ? s + L - t : nx;
+            const SlabRange planes = slab_range(nx, L, s, t);
+            g.ia = planes.ia;
+            g.ib = planes.ib;
             prof_begin(h, 0, row * (double)(g.ib - g.ia), r);
             launch_h3d<T>(g, none, f, c, Ei_at(h, t), h->stream);
             prof_end(h, r);

@@ -269,6 +269,28 @@ def test_3d_slabs_bitwise(G, prec, nx, slots):
     assert all(np.array_equal(a, b) for a, b in zip(got["fused"], got["split"]))
 
 
+@pytest.mark.parametrize("nx,x_planes", [(25, 1), (27, 5), (30, 1), (30, 13)])
+def test_3d_slabs_of_few_planes_bitwise(G, nx, x_planes):
+    """The shortest grids that are stepped in slabs, with the planes a thread
+    walks set by the caller, against the one-pass executor: the same bits, the
+    sample points of every plane included."""
+    ny, nz = 700, 620
+    p = W.sphere_c3(60, cpml=3, n_freqs=2, box_dft=False)
+    wp2 = np.zeros((3, nx, ny, nz))
+    wp2[:, 4:nx - 4, 12:300, 14:250] = p.wp2.max()
+    pts = np.array([(c, i, 20 + 3 * i, 30 + c) for i in range(nx) for c in (0, 2, 4)], np.int32)
+    p = p.copy(nx=nx, ny=ny, nz=nz, wp2=wp2, nu=np.full((nx, ny, nz), 1e10), b0=6, b1=nx - 5, points=pts)
+    got = {}
+    for ex in ("fused", "split"):
+        say(f"case 3d short slabs {nx}x{ny}x{nz} x_planes={x_planes} {ex}")
+        with G.FdtdPlasma3D(p, precision="f32", exec=ex, x_planes=x_planes if ex == "split" else 0) as h:
+            h.run(19)
+            h.step(40)
+            got[ex] = [h.field(nm) for nm in ("Ex", "Hy", "Jx")] + [h.spectra()]
+    assert np.any(got["split"][2])
+    assert all(np.array_equal(a, b) for a, b in zip(got["fused"], got["split"]))
+
+
 def test_3d_c3_full_size_vacuum_properties(G):
     """384^3 in the benchmark's configuration with the plasma off: the
     scattered-field region stays quiet, the total-field region carries exactly

@@ -980,9 +980,36 @@ void flush(fdtd_plasma *h)
     h->win_base = h->steps;
 }
 
+// The side streams start behind the handle's stream (fork) and the handle's
+// stream goes on behind them (join).
+hipError_t fork_side(fdtd_plasma *h)
+{
+    hipError_t e = hipEventRecord(h->ev_fork, h->stream);
+    if (e == hipSuccess) e = hipStreamWaitEvent(h->side, h->ev_fork, 0);
+    if (e == hipSuccess && h->side2) e = hipStreamWaitEvent(h->side2, h->ev_fork, 0);
+    return e;
+}
+hipError_t join_side(fdtd_plasma *h)
+{
+    hipError_t e = hipEventRecord(h->ev_join, h->side);
+    if (e == hipSuccess) e = hipStreamWaitEvent(h->stream, h->ev_join, 0);
+    if (e == hipSuccess && h->side2) e = hipEventRecord(h->ev_join2, h->side2);
+    if (e == hipSuccess && h->side2) e = hipStreamWaitEvent(h->stream, h->ev_join2, 0);
+    return e;
+}
+
+// The streams of a pass do not wait for each other as they should: the handle's
+// state is unknown from here on.
+int lost_state(fdtd_plasma *h, hipError_t e)
+{
+    h->poisoned = true;
+    return fail(FDTD_E_DEVICE, "side stream failed: %s", hipGetErrorString(e));
+}
+
 template <typename T>
 int advance_t(fdtd_plasma *h, int64_t nsteps)
 {
+    hipError_t e;
     const Grids g = h->grids();
     State<T> s = h->state<T>();
     int64_t left = nsteps;
@@ -1027,19 +1054,15 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
             };
             auto on_side = [&](int c) { return fork && c >= 2; };
             if (fork) {
-                (void)hipEventRecord(h->ev_fork, h->stream);
-                (void)hipStreamWaitEvent(h->side, h->ev_fork, 0);
+                if ((e = fork_side(h)) != hipSuccess) return lost_state(h, e);
                 if (h->side2) {
-                    (void)hipStreamWaitEvent(h->side2, h->ev_fork, 0);
                     launch_class<T>(h, g, s, h->cur, 2, (int)k, slot, h->side);
                     launch_class<T>(h, g, s, h->cur, 3, (int)k, slot, h->side2);
-                    (void)hipEventRecord(h->ev_join2, h->side2);
                 } else {
                     for (int c = 2; c < kTileClasses; ++c)
                         launch_class<T>(h, g, s, h->cur, c, (int)k, slot, h->side);
                     segments(h->side);
                 }
-                (void)hipEventRecord(h->ev_join, h->side);
             }
             for (int c = 0; c < kTileClasses; ++c)
                 if (h->ntiles[c] && !on_side(c)) {
@@ -1052,10 +1075,7 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
                 segments(h->stream);
                 prof_end(h);
             }
-            if (fork) {
-                (void)hipStreamWaitEvent(h->stream, h->ev_join, 0);
-                if (h->side2) (void)hipStreamWaitEvent(h->stream, h->ev_join2, 0);
-            }
+            if (fork && (e = join_side(h)) != hipSuccess) return lost_state(h, e);
         } else if (h->exec == FDTD_EXEC_MIXED) {
             // bins and tiles hold disjoint grids.  The bins advance the whole
             // window in one launch (beside the tiles on the side stream, unless
@@ -1065,15 +1085,11 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
             const int out = h->cur ^ (int)(passes & 1);
             const bool fork = h->side && !h->profiling;
             hipStream_t rs = fork ? h->side : h->stream;
-            if (fork) {
-                (void)hipEventRecord(h->ev_fork, h->stream);
-                (void)hipStreamWaitEvent(h->side, h->ev_fork, 0);
-            }
+            if (fork && (e = fork_side(h)) != hipSuccess) return lost_state(h, e);
             prof_begin(h, "resident", h->class_nodes[kTileClasses]);
             launch_group<T>(g, s, h->cur, out, h->d_slots, h->nbins, h->resWaves, h->resC, (int)k, slot,
                                rs);
             prof_end(h);
-            if (fork) (void)hipEventRecord(h->ev_join, h->side);
             int cur = h->cur;
             for (int64_t done = 0; done < k; done += h->Kh) {
                 const int kk = (int)std::min<int64_t>(h->Kh, k - done);
@@ -1085,7 +1101,7 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
                     }
                 cur ^= 1;
             }
-            if (fork) (void)hipStreamWaitEvent(h->stream, h->ev_join, 0);
+            if (fork && (e = join_side(h)) != hipSuccess) return lost_state(h, e);
             h->cur = out ^ 1;          // flipped back below
         } else {
             k = std::min<int64_t>(left, room);
@@ -1099,8 +1115,8 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
         left -= k;
         if (h->steps - h->win_base == h->SB) flush(h);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(FDTD_E_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
+    if ((e = hipGetLastError()) != hipSuccess)
+        return fail(FDTD_E_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
     return FDTD_OK;
 }
 
@@ -1427,10 +1443,24 @@ int fdtd_plasma_run(fdtd_plasma *h, int64_t nsteps)
         return rc;
     }
     const int64_t key = nsteps * 2 + (h->ck_on ? 1 : 0);
+    // until the graph is launched nothing has run: a failure leaves the state
+    // the handle had
+    const int cur = h->cur;
+    const int64_t steps = h->steps, win_base = h->win_base;
+    auto not_run = [&](int code) {
+        h->cur = cur;
+        h->steps = steps;
+        h->win_base = win_base;
+        h->ck_on = h->poisoned = false;
+        (void)hipGetLastError();       // reported here, not by the next call too
+        return code;
+    };
+    hipError_t e;
     auto it = h->graphs.find(key);
     if (it == h->graphs.end()) {
         // capture reset + the whole time loop once for this length
-        HIP_TRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
+        e = hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal);
+        if (e != hipSuccess) return not_run(fail(FDTD_E_DEVICE, "begin capture failed: %s", hipGetErrorString(e)));
         reset(h);
         rc = advance(h, nsteps);
         // the run's last, partially filled sample window is folded into the
@@ -1438,13 +1468,16 @@ int fdtd_plasma_run(fdtd_plasma *h, int64_t nsteps)
         // as a later step() continuing the window expects them)
         if (rc == FDTD_OK && nsteps > 0) spectra_to_tmp(h);
         hipGraph_t graph = nullptr;
-        hipError_t e = hipStreamEndCapture(h->stream, &graph);
-        if (rc) { h->ck_on = false; if (graph) (void)hipGraphDestroy(graph); return rc; }
-        if (e != hipSuccess) return fail(FDTD_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
+        e = hipStreamEndCapture(h->stream, &graph);
+        if (rc || e != hipSuccess) {
+            if (graph) (void)hipGraphDestroy(graph);
+            return not_run(rc ? rc : fail(FDTD_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e)));
+        }
         hipGraphExec_t exec = nullptr;
         e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
         (void)hipGraphDestroy(graph);
-        if (e != hipSuccess) return fail(FDTD_E_DEVICE, "graph instantiate failed: %s", hipGetErrorString(e));
+        if (e != hipSuccess)
+            return not_run(fail(FDTD_E_DEVICE, "graph instantiate failed: %s", hipGetErrorString(e)));
         it = h->graphs.emplace(key, exec).first;
     } else {
         // bookkeeping identical to what the captured launches did
@@ -1466,7 +1499,8 @@ int fdtd_plasma_run(fdtd_plasma *h, int64_t nsteps)
             if (h->steps - h->win_base == h->SB) h->win_base = h->steps;
         }
     }
-    HIP_TRY(hipGraphLaunch(it->second, h->stream));
+    e = hipGraphLaunch(it->second, h->stream);
+    if (e != hipSuccess) return not_run(fail(FDTD_E_DEVICE, "graph launch failed: %s", hipGetErrorString(e)));
     h->tmp_valid = nsteps > 0;
     h->ck_valid = h->ck_on;
     h->ck_run = nsteps;
@@ -1812,19 +1846,16 @@ int fdtd_plasma_destroy(fdtd_plasma *h)
 {
     if (!h) return FDTD_OK;
     (void)hipStreamSynchronize(h->stream);
-    if (h->side) {
-        (void)hipStreamSynchronize(h->side);
-        (void)hipStreamDestroy(h->side);
-    }
-    if (h->side2) {
-        (void)hipStreamSynchronize(h->side2);
-        (void)hipStreamDestroy(h->side2);
-    }
+    if (h->side) (void)hipStreamSynchronize(h->side);
+    if (h->side2) (void)hipStreamSynchronize(h->side2);
+    // the graphs before the streams and events they were captured through
+    for (auto &kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
+    for (auto &kv : h->adj_graphs) (void)hipGraphExecDestroy(kv.second);
+    if (h->side) (void)hipStreamDestroy(h->side);
+    if (h->side2) (void)hipStreamDestroy(h->side2);
     if (h->ev_fork) (void)hipEventDestroy(h->ev_fork);
     if (h->ev_join) (void)hipEventDestroy(h->ev_join);
     if (h->ev_join2) (void)hipEventDestroy(h->ev_join2);
-    for (auto &kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
-    for (auto &kv : h->adj_graphs) (void)hipGraphExecDestroy(kv.second);
     if (h->owns_ws && h->ws) (void)hipFree(h->ws);
     if (h->static_ws) {
         std::lock_guard<std::mutex> lock(g_static_mu);

@@ -277,6 +277,7 @@ struct fdtd2d {
     double2 *X = nullptr, *Xtmp = nullptr, *tw = nullptr;
     int64_t steps = 0, win_base = 0;
     bool tmp_valid = false;
+    bool lost = false;                       // the streams of a pass did not wait for each other: state unknown
     hipStream_t side = nullptr;              // plasma tiles beside the vacuum tiles (default priority)
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     std::map<int64_t, hipGraphExec_t> graphs;
@@ -336,9 +337,22 @@ Fields2<T> copy2(const fdtd2d *h, int i)
     return f;
 }
 
-template <typename T>
-void advance2_t(fdtd2d *h, int64_t n)
+// The side stream starts behind the handle's (fork), which goes on behind it (join).
+hipError_t fork2(fdtd2d *h)
 {
+    const hipError_t e = hipEventRecord(h->ev_fork, h->stream);
+    return e == hipSuccess ? hipStreamWaitEvent(h->side, h->ev_fork, 0) : e;
+}
+hipError_t join2(fdtd2d *h)
+{
+    const hipError_t e = hipEventRecord(h->ev_join, h->side);
+    return e == hipSuccess ? hipStreamWaitEvent(h->stream, h->ev_join, 0) : e;
+}
+
+template <typename T>
+hipError_t advance2_t(fdtd2d *h, int64_t n)
+{
+    hipError_t e = hipSuccess;
     while (n > 0) {
         const int slot = (int)(h->steps - h->win_base);
         if (slot == 0 && h->g.has_src) launch_src2d(h->g, h->steps + 1, kSB2, h->srcv, h->stream);
@@ -346,16 +360,16 @@ void advance2_t(fdtd2d *h, int64_t n)
         const Fields2<T> in = copy2<T>(h, h->cur), out = copy2<T>(h, h->cur ^ 1);
         // plasma and vacuum tiles write disjoint cells: side by side
         const int64_t nvac = (int64_t)h->p.tiles.size() - h->p.nplasma;
-        if (h->side) {
-            (void)hipEventRecord(h->ev_fork, h->stream);
-            (void)hipStreamWaitEvent(h->side, h->ev_fork, 0);
+        if (h->side && (e = fork2(h)) != hipSuccess) {
+            h->lost = true;
+            return e;
         }
         launch_tiles2d<T>(h->g, in, out, h->tiles, h->p.nplasma, Tiles2::plasma, k, slot,
                           h->side ? h->side : h->stream);
         launch_tiles2d<T>(h->g, in, out, h->tiles + h->p.nplasma, nvac, h->p.vac, k, slot, h->stream);
-        if (h->side) {
-            (void)hipEventRecord(h->ev_join, h->side);
-            (void)hipStreamWaitEvent(h->stream, h->ev_join, 0);
+        if (h->side && (e = join2(h)) != hipSuccess) {
+            h->lost = true;
+            return e;
         }
         h->cur ^= 1;
         h->steps += k;
@@ -365,14 +379,20 @@ void advance2_t(fdtd2d *h, int64_t n)
             h->win_base = h->steps;
         }
     }
+    return hipGetLastError();
 }
 
 int advance2(fdtd2d *h, int64_t n)
 {
-    if (h->p.es == 8) advance2_t<double>(h, n);
-    else advance2_t<float>(h, n);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail2(FDTD_E_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
+    const hipError_t e = h->p.es == 8 ? advance2_t<double>(h, n) : advance2_t<float>(h, n);
+    if (e != hipSuccess) return fail2(FDTD_E_DEVICE, "time loop failed: %s", hipGetErrorString(e));
+    return FDTD_OK;
+}
+
+int check2(const fdtd2d *h)
+{
+    if (!h) return fail2(FDTD_E_INVALID, "handle is NULL");
+    if (h->lost) return fail2(FDTD_E_STATE, "handle used after a device failure");
     return FDTD_OK;
 }
 
@@ -515,7 +535,8 @@ int fdtd2d_create(const fdtd2d_desc *desc, void *workspace, size_t bytes, fdtd2d
 
 int fdtd2d_step(fdtd2d *h, int64_t nsteps)
 {
-    if (!h) return fail2(FDTD_E_INVALID, "handle is NULL");
+    int rc = check2(h);
+    if (rc) return rc;
     if (nsteps < 0) return fail2(FDTD_E_INVALID, "nsteps %lld < 0", (long long)nsteps);
     h->tmp_valid = false;
     return advance2(h, nsteps);
@@ -523,34 +544,49 @@ int fdtd2d_step(fdtd2d *h, int64_t nsteps)
 
 int fdtd2d_run(fdtd2d *h, int64_t nsteps)
 {
-    if (!h) return fail2(FDTD_E_INVALID, "handle is NULL");
+    int rc = check2(h);
+    if (rc) return rc;
     if (nsteps < 0) return fail2(FDTD_E_INVALID, "nsteps %lld < 0", (long long)nsteps);
     h->tmp_valid = false;
     if (h->stream == nullptr) {   // the legacy null stream cannot be captured
         reset2(h);
-        int rc = advance2(h, nsteps);
+        rc = advance2(h, nsteps);
         if (rc) return rc;
         to_tmp(h);
         h->tmp_valid = nsteps > 0;
         return FDTD_OK;
     }
+    // until the graph is launched nothing has run: a failure leaves the state
+    // the handle had
+    const int cur = h->cur;
+    const int64_t steps = h->steps, win_base = h->win_base;
+    auto not_run = [&](int code) {
+        h->cur = cur;
+        h->steps = steps;
+        h->win_base = win_base;
+        h->lost = false;
+        (void)hipGetLastError();       // reported here, not by the next call too
+        return code;
+    };
+    hipError_t e;
     auto it = h->graphs.find(nsteps);
     if (it == h->graphs.end()) {
-        HIP_TRY2(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
+        e = hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal);
+        if (e != hipSuccess) return not_run(fail2(FDTD_E_DEVICE, "begin capture failed: %s", hipGetErrorString(e)));
         reset2(h);
-        int rc = advance2(h, nsteps);
+        rc = advance2(h, nsteps);
         if (rc == FDTD_OK) to_tmp(h);
         hipGraph_t graph = nullptr;
-        hipError_t e = hipStreamEndCapture(h->stream, &graph);
-        if (rc) {
+        e = hipStreamEndCapture(h->stream, &graph);
+        if (rc || e != hipSuccess) {
             if (graph) (void)hipGraphDestroy(graph);
-            return rc;
+            return not_run(rc ? rc : fail2(FDTD_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e)));
         }
-        if (e != hipSuccess) return fail2(FDTD_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
         hipGraphExec_t ex = nullptr;
         e = hipGraphInstantiate(&ex, graph, nullptr, nullptr, 0);
         (void)hipGraphDestroy(graph);
-        if (e != hipSuccess) return fail2(FDTD_E_DEVICE, "graph instantiate failed: %s", hipGetErrorString(e));
+        if (e != hipSuccess)
+            return not_run(fail2(FDTD_E_DEVICE, "graph instantiate failed: %s", hipGetErrorString(e)));
         it = h->graphs.emplace(nsteps, ex).first;
     } else {
         h->steps = nsteps;
@@ -559,14 +595,16 @@ int fdtd2d_run(fdtd2d *h, int64_t nsteps)
         static_assert(kSB2 % kSteps2 == 0, "windows hold whole passes");
         h->cur = (int)(((nsteps + kSteps2 - 1) / kSteps2) & 1);
     }
-    HIP_TRY2(hipGraphLaunch(it->second, h->stream));
+    e = hipGraphLaunch(it->second, h->stream);
+    if (e != hipSuccess) return not_run(fail2(FDTD_E_DEVICE, "graph launch failed: %s", hipGetErrorString(e)));
     h->tmp_valid = nsteps > 0;
     return FDTD_OK;
 }
 
 int fdtd2d_spectra(fdtd2d *h, double *re, double *im)
 {
-    if (!h) return fail2(FDTD_E_INVALID, "handle is NULL");
+    int rc = check2(h);
+    if (rc) return rc;
     if (!re || !im) return fail2(FDTD_E_INVALID, "output pointer is NULL");
     if (h->steps == 0 || h->d.n_probes == 0) return fail2(FDTD_E_STATE, "no step taken yet, or no probes");
     if (!h->tmp_valid) to_tmp(h);
@@ -585,7 +623,8 @@ int fdtd2d_spectra(fdtd2d *h, double *re, double *im)
 
 int fdtd2d_get_fields(fdtd2d *h, int32_t which, double *out)
 {
-    if (!h) return fail2(FDTD_E_INVALID, "handle is NULL");
+    int rc = check2(h);
+    if (rc) return rc;
     if (!out) return fail2(FDTD_E_INVALID, "output pointer is NULL");
     const Plan2 &p = h->p;
     if (which < 0 || which >= 2 * p.ncomp + p.nh) return fail2(FDTD_E_INVALID, "which %d out of range", which);

@@ -1,0 +1,124 @@
+"""The library's host side over a stand-in HIP runtime (hip_stub.cpp, preloaded
+into a child process): in which order a handle lets go of what its graphs were
+captured through, and what a handle holds after a capture that failed.  No
+kernel runs."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+CHILD = r"""
+import ctypes, sys, types
+import numpy as np
+sys.modules["torch"] = types.ModuleType("torch")     # the binding only loads its HIP runtime
+from paper_1709_00821_amd import _lib as L, workloads as W
+from paper_1709_00821_amd.plasma import make_desc
+from paper_1709_00821_amd.plasma2d import make_desc2
+lib, stub, STREAM = L.lib(), ctypes.CDLL(sys.argv[1]), 64     # any stream but the null one
+stub.stub_waits.restype = stub.stub_launches.restype = stub.stub_bad_grids.restype = ctypes.c_long
+
+def long_1d(**kw):
+    p = W.slab_c1(n=300000, slab=(100000, 200000), src=5000, probes=(3000, 250000), n_freqs=4)
+    d, keep = make_desc(p, "f64", "tiled", stream_handle=STREAM, **kw)
+    h = ctypes.c_void_p()
+    L.check(lib.fdtd_plasma_create(ctypes.byref(d), None, 0, ctypes.byref(h)))
+    return h
+
+def grid_2d():
+    p = W.cylinder_2d("tm", n=400, steps=10)
+    d, keep = make_desc2(p, "f64", STREAM)
+    h = ctypes.c_void_p()
+    L.check2(lib.fdtd2d_create(ctypes.byref(d), None, 0, ctypes.byref(h)))
+    return h
+
+def done(h, fn):
+    v = ctypes.c_int64()
+    assert fn(h, ctypes.byref(v)) == 0
+    return v.value
+"""
+
+ORDER = CHILD + r"""
+for make, run, destroy in ((long_1d, lib.fdtd_plasma_run, lib.fdtd_plasma_destroy),
+                           (grid_2d, lib.fdtd2d_run, lib.fdtd2d_destroy)):
+    h = make()
+    for T in (100, 130, 100):
+        assert run(h, T) == 0
+    assert stub.stub_live() == 5              # a side stream, two events, two graphs
+    assert destroy(h) == 0
+    assert stub.stub_live() == 0 and stub.stub_misuses() == 0, stub.stub_misuses()
+assert stub.stub_waits() > 0 and stub.stub_bad_grids() == 0
+"""
+
+FAILED = CHILD + r"""
+what = sys.argv[2]
+for make, run, step, count, destroy in (
+        (lambda: long_1d(checkpoint=200), lib.fdtd_plasma_run, lib.fdtd_plasma_step, lib.fdtd_plasma_steps_done,
+         lib.fdtd_plasma_destroy),
+        (grid_2d, lib.fdtd2d_run, lib.fdtd2d_step, lib.fdtd2d_steps_done, lib.fdtd2d_destroy)):
+    h = make()
+    assert step(h, 20) == 0
+    before = stub.stub_launches()
+    assert step(h, 20) == 0
+    pass_ = stub.stub_launches() - before     # the launches of 20 steps inside a sample window
+    if what == "hipGraphLaunch":
+        assert run(h, 100) == 0               # a graph that is there already
+        assert run(h, 40) == 0
+    stub.stub_fail(what.encode())
+    assert run(h, 100) == L.E_DEVICE
+    assert done(h, count) == 40               # nothing ran: the state is the one before
+    before = stub.stub_launches()
+    assert step(h, 20) == 0
+    assert stub.stub_launches() - before == pass_, "the step of a run that failed"
+    assert run(h, 100) == 0 and done(h, count) == 100
+    assert run(h, 7) == 0 and done(h, count) == 7
+    destroy(h)
+    assert stub.stub_live() == 0 and stub.stub_misuses() == 0
+"""
+
+EVENTS = CHILD + r"""
+what = sys.argv[2]
+for make, step, err, destroy in ((long_1d, lib.fdtd_plasma_step, lib.fdtd_plasma_last_error, lib.fdtd_plasma_destroy),
+                                 (grid_2d, lib.fdtd2d_step, lib.fdtd2d_last_error, lib.fdtd2d_destroy)):
+    h = make()
+    assert step(h, 10) == 0
+    stub.stub_fail(what.encode())
+    assert step(h, 10) == L.E_DEVICE          # launches beside each other without their wait
+    assert step(h, 10) == L.E_STATE
+    destroy(h)
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = tmp_path_factory.mktemp("stub") / "hip_stub.so"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-w", os.path.join(HERE, "hip_stub.cpp"), "-o", str(so)], check=True)
+    return str(so)
+
+
+def child(code, stub, *args):
+    from paper_1709_00821_amd import build
+    if not os.path.exists(build.LIB):
+        build.build()
+    r = subprocess.run([sys.executable, "-c", code, stub, *args], cwd=ROOT, capture_output=True, text=True,
+                       env={**os.environ, "LD_PRELOAD": stub, "PYTHONPATH": ROOT}, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_graphs_go_before_what_they_were_captured_through(stub):
+    child(ORDER, stub)
+
+
+@pytest.mark.parametrize("what", ["hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphInstantiate",
+                                  "hipGraphLaunch"])
+def test_a_run_that_was_not_captured_leaves_the_state(stub, what):
+    child(FAILED, stub, what)
+
+
+@pytest.mark.parametrize("what", ["hipEventRecord", "hipStreamWaitEvent"])
+def test_a_step_whose_streams_did_not_wait_is_reported(stub, what):
+    child(EVENTS, stub, what)

@@ -65,7 +65,9 @@ struct Plan2 {
     std::vector<Tile2> tiles;        // the plasma tiles, then the vacuum tiles
     int64_t nplasma = 0;
     Tiles2 vac = Tiles2::flat;       // shape of the vacuum tiles
-    std::vector<int4> tprobe;        // probes by tile
+    std::vector<LaneProbes> tprobe;  // probes by tile, wave and lane
+    std::vector<int32_t> row;        // sample row of each probe (probes of the same cell and component share one)
+    int64_t rows = 0;
     int64_t o_E[2][2] = {}, o_H[2][2] = {}, o_J[2][2] = {};   // [copy][component]
     int64_t o_span = 0, o_rowoff = 0, o_wp2[2] = {0, 0}, o_nu[2] = {0, 0}, o_tiles = 0,
             o_tprobe = 0, o_srcv = 0, o_freqs = 0, o_samp = 0, o_X = 0, o_Xtmp = 0, o_tw = 0;
@@ -190,20 +192,40 @@ void build_tiles2(const fdtd2d_desc *d, Plan2 &p)
     }
     p.nplasma = (int64_t)p.tiles.size();
     p.tiles.insert(p.tiles.end(), vac.begin(), vac.end());
-    // each probe with the tile that writes it (probes in order of their rows)
+    // each probe with the tile that writes it, by wave, lane and register
     std::vector<std::pair<int64_t, int>> by_row;
     for (int k = 0; k < d->n_probes; ++k) by_row.push_back({d->probes[3 * k + 1], k});
     std::sort(by_row.begin(), by_row.end());
     p.tprobe.clear();
-    for (Tile2 &t : p.tiles) {
-        t.probe0 = (int32_t)p.tprobe.size();
+    p.row.assign(d->n_probes, 0);
+    p.rows = 0;
+    for (size_t n = 0; n < p.tiles.size(); ++n) {
+        Tile2 &t = p.tiles[n];
+        const Shape2 &sh = (int64_t)n < p.nplasma ? q : v;
+        std::vector<std::pair<int64_t, int>> in;      // (wave, lane, bit) as one number, probe
         auto at = std::lower_bound(by_row.begin(), by_row.end(), std::make_pair((int64_t)t.oi0, -1));
         for (; at != by_row.end() && at->first < t.oi1; ++at) {
             const int64_t *pr = d->probes + 3 * at->second;
-            if (pr[2] >= t.oj0 && pr[2] < t.oj1)
-                p.tprobe.push_back(make_int4((int)(pr[1] - t.i0), (int)(pr[2] - t.j0), (int)pr[0], at->second));
+            if (pr[2] < t.oj0 || pr[2] >= t.oj1) continue;
+            const int64_t i = pr[1] - t.i0, j = pr[2] - t.j0;
+            const int64_t bit = (pr[0] * sh.R + i % sh.R) * sh.CJ + j % sh.CJ;
+            in.push_back({(i / sh.R * 64 + j / sh.CJ) * 32 + bit, at->second});
         }
-        t.nprobe = (int32_t)p.tprobe.size() - t.probe0;
+        std::sort(in.begin(), in.end());
+        t.probe0 = (int32_t)(p.tprobe.size() / 64);
+        t.pwaves = 0;
+        for (size_t k = 0; k < in.size(); ++k) {
+            const int64_t bit = in[k].first % 32, lane = in[k].first / 32 % 64, w = in[k].first / 2048;
+            if (!((t.pwaves >> w) & 1)) {
+                t.pwaves |= 1 << w;
+                p.tprobe.resize(p.tprobe.size() + 64, LaneProbes{0, 0});
+            }
+            LaneProbes &lp = p.tprobe[p.tprobe.size() - 64 + lane];
+            if (!lp.mask) lp.first = (int32_t)p.rows;
+            if (!((lp.mask >> bit) & 1)) ++p.rows;
+            lp.mask |= 1u << bit;
+            p.row[in[k].second] = (int32_t)(p.rows - 1);
+        }
     }
 }
 
@@ -250,7 +272,7 @@ int plan2(const fdtd2d_desc *d, Plan2 &p)
     }
     const int P = std::max(d->n_probes, 1);
     p.o_tiles = L.take((int64_t)sizeof(Tile2) * (int64_t)p.tiles.size());
-    p.o_tprobe = L.take(16 * P);
+    p.o_tprobe = L.take((int64_t)sizeof(LaneProbes) * (int64_t)p.tprobe.size());
     p.o_srcv = L.take(8 * kSB2);
     p.o_freqs = L.take(8 * d->n_freqs);
     p.o_samp = L.take(8 * (int64_t)P * kSB2);
@@ -314,8 +336,7 @@ void fold(fdtd2d *h, double2 *dst)
     const int count = (int)(h->steps - h->win_base);
     if (h->d.n_probes > 0 && count > 0)
         launch_dft(dft_view(h), h->freqs, h->d.n_freqs, h->win_base + 1, count, h->tw,
-                   std::min(kSB2, kTwiddleChunk), dst, h->d.n_probes,
-                   h->stream);
+                   std::min(kSB2, kTwiddleChunk), dst, h->p.rows, h->stream);
 }
 
 void to_tmp(fdtd2d *h)
@@ -468,14 +489,13 @@ int fdtd2d_create(const fdtd2d_desc *desc, void *workspace, size_t bytes, fdtd2d
     h->tiles = (Tile2 *)(w + p.o_tiles);
     h->srcv = (double *)(w + p.o_srcv);
     g.srcv = h->srcv;
-    g.tprobe = (const int4 *)(w + p.o_tprobe);
+    g.tprobe = (const LaneProbes *)(w + p.o_tprobe);
     g.has_src = desc->has_src != 0;
     g.si = desc->src_i;
     g.sj = desc->src_j;
     g.src_tau = desc->src_tau;
     g.src_t0 = desc->src_t0;
     g.src_amp = desc->src_amp;
-    g.P = desc->n_probes;
     g.SB = kSB2;
     h->samp = g.samp = (double *)(w + p.o_samp);
     h->freqs = (double *)(w + p.o_freqs);
@@ -507,7 +527,7 @@ int fdtd2d_create(const fdtd2d_desc *desc, void *workspace, size_t bytes, fdtd2d
         H2D(w + p.o_nu[c], cn.data() + c * p.S, 8 * p.S);
     }
     H2D(h->tiles, p.tiles.data(), sizeof(Tile2) * p.tiles.size());
-    H2D(w + p.o_tprobe, p.tprobe.data(), 16 * p.tprobe.size());
+    H2D(w + p.o_tprobe, p.tprobe.data(), sizeof(LaneProbes) * p.tprobe.size());
     H2D(w + p.o_freqs, desc->freqs_hz, 8 * (size_t)desc->n_freqs);
     // the legacy null stream takes every launch itself
     if (e == hipSuccess && st && p.nplasma > 0 && p.nplasma < (int64_t)p.tiles.size()) {
@@ -614,9 +634,10 @@ int fdtd2d_spectra(fdtd2d *h, double *re, double *im)
     HIP_TRY2(hipStreamSynchronize(h->stream));
     bool finite = true;
     for (int64_t i = 0; i < n; ++i) {
-        re[i] = X[i].x;
-        im[i] = X[i].y;
-        finite = finite && std::isfinite(X[i].x) && std::isfinite(X[i].y);
+        const double2 x = X[(int64_t)h->p.row[i / h->d.n_freqs] * h->d.n_freqs + i % h->d.n_freqs];
+        re[i] = x.x;
+        im[i] = x.y;
+        finite = finite && std::isfinite(x.x) && std::isfinite(x.y);
     }
     return finite ? FDTD_OK : fail2(FDTD_E_NONFINITE, "a probe spectrum holds NaN or Inf");
 }

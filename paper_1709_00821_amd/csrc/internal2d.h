@@ -8,6 +8,14 @@
 
 namespace fdtdp {
 
+// The probes in the cells of one lane of a tile: bit (q R + r) CJ + c for
+// component q at row r and column c of its registers.  Their sample rows follow
+// one another from `first` in the order of the bits.
+struct LaneProbes {
+    uint32_t mask;
+    int32_t first;
+};
+
 // Device view of a 2D grid (passed by value to kernels).  The plasma lives on
 // a compact support: row i holds it on j in [span[i].x, span[i].y), at compact
 // index rowoff[i] + j - span[i].x of the per-component arrays (the union of
@@ -25,9 +33,9 @@ struct Grid2 {
     int64_t si, sj;
     double src_tau, src_t0, src_amp;
     const double *srcv;        // [SB] source value of every step of the current window
-    int P, SB;                 // probes, sample window length
-    const int4 *tprobe;        // probes by tile: row and column in the tile, component, probe
-    double *samp;              // [P][SB]
+    int SB;                    // sample window length
+    const LaneProbes *tprobe;  // [waves with probes][64]
+    double *samp;              // [distinct probes][SB]
 };
 
 template <typename T>
@@ -43,7 +51,7 @@ struct Fields2 {
 struct Tile2 {
     int32_t i0, j0, oi0, oi1, oj0, oj1;
     int32_t special;           // holds cells outside the grid, a wall line or the source
-    int32_t probe0, nprobe;    // its part of tprobe
+    int32_t pwaves, probe0;    // its waves with probes (a bit each) and the first one's place in tprobe
     int32_t pad[3];
 };
 

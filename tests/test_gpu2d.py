@@ -118,6 +118,32 @@ def test_tile_edges_match_oracle(G, mode, nx, ny, px, py):
             assert np.array_equal(G2[k], F2[k]), (prec, k)
 
 
+@pytest.mark.parametrize("mode,nx,ny,px,py", [("tm", 70, 90, False, False), ("te", 97, 130, True, False),
+                                              ("te", 820, 1040, False, True)])
+def test_2d_dense_probes_match_fields(G, mode, nx, ny, px, py):
+    """Probes on every cell of a block (both E components in TE) that crosses
+    tiles of plasma and vacuum, waves and lanes, some given twice and in no
+    order: after one step their spectra at f = 0 are dt times the E fields, and
+    after 21 those of the oracle."""
+    rng = np.random.default_rng(nx)
+    p = W.random_2d(rng, mode, nx, ny, periodic_x=px, periodic_y=py)
+    nc = 1 if mode == "tm" else 2
+    i0, j0 = int(rng.integers(0, nx - 40)), int(rng.integers(0, ny - 50))
+    pr = np.array([(c, i, j) for c in range(nc) for i in range(i0, i0 + 40) for j in range(j0, j0 + 50)], np.int64)
+    pr = np.concatenate([pr, pr[rng.integers(0, len(pr), 90)]])[:4096]
+    p = p.copy(probes=pr[rng.permutation(len(pr))], freqs=np.array([0.0, 3e10]), src=(i0 + 20, j0 + 25))
+    say(f"case 2d dense probes {mode} {nx}x{ny}")
+    for prec in ("f64", "f32"):
+        with G.FdtdPlasma2D(p, precision=prec) as h:
+            X, E = h.step(1).spectra(), h.fields()["E"]
+            want = p.dt * E[tuple(p.probes.T)]
+            assert np.any(want) and np.array_equal(X[:, 0], want), prec
+            h.step(20)
+            X = h.spectra()
+        ref = oracle.run2d(p, 21, kind="omp")["X"]
+        assert rel(X, ref) <= (1e-12 if prec == "f64" else 2e-5), prec
+
+
 def test_2d_step_composition_and_replay(G):
     p = W.random_2d(np.random.default_rng(5), "te", 70, 90)
     say("case 2d step composition")

@@ -70,15 +70,19 @@ typedef struct {
     void *stream;                /* hipStream_t for every launch and copy; NULL = null stream */
 } fdtd2d_desc;
 
-/* Device bytes the handle needs (fields, plasma support, samples, spectra);
- * the descriptor is validated as for create. */
+/* Device bytes of the handle's fast path (two copies of the fields and
+ * currents, plasma support, samples, spectra); the descriptor is validated as
+ * for create.  Less does too: see create. */
 int fdtd2d_workspace_bytes(const fdtd2d_desc *desc, size_t *bytes);
 
 /* Validate, lay out the workspace, copy the host arrays (borrowed for the call
  * only) and zero the state; the per-cell coefficients of eqs.(11)+(12) are
  * formed where a tile loads them, from wp2 and nu.  workspace: 256-byte aligned device memory of at
  * least fdtd2d_workspace_bytes, owned by the caller and outliving the handle,
- * or NULL (the library allocates and owns it).  On failure *out is NULL.
+ * or NULL (the library allocates and owns it).  A workspace, or a card, that
+ * holds only one copy of the fields and currents (about half) is taken too: every step then
+ * updates them in place, one at a time, with the same results several times as
+ * slowly.  On failure *out is NULL.
  * Errors: FDTD_E_INVALID (a field out of range, a NaN or negative wp2/nu,
  * a source or probe outside the grid), FDTD_E_UNSTABLE (Courant number above
  * 1/sqrt(2)), FDTD_E_WORKSPACE, FDTD_E_DEVICE. */

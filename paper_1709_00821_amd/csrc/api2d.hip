@@ -67,10 +67,13 @@ struct Plan2 {
     Tiles2 vac = Tiles2::flat;       // shape of the vacuum tiles
     std::vector<LaneProbes> tprobe;  // probes by tile, wave and lane
     std::vector<int32_t> row;        // sample row of each probe (probes of the same cell and component share one)
+    std::vector<int64_t> cell;       // component N + cell of each sample row
     int64_t rows = 0;
+    bool one = false;                // one copy of the fields: every step in place
+    bool thin = false;               // two copies would not be used
     int64_t o_E[2][2] = {}, o_H[2][2] = {}, o_J[2][2] = {};   // [copy][component]
     int64_t o_span = 0, o_rowoff = 0, o_wp2[2] = {0, 0}, o_nu[2] = {0, 0}, o_tiles = 0,
-            o_tprobe = 0, o_srcv = 0, o_freqs = 0, o_samp = 0, o_X = 0, o_Xtmp = 0, o_tw = 0;
+            o_tprobe = 0, o_cell = 0, o_srcv = 0, o_freqs = 0, o_samp = 0, o_X = 0, o_Xtmp = 0, o_tw = 0;
 };
 
 int validate2(const fdtd2d_desc *d)
@@ -142,6 +145,7 @@ void build_tiles2(const fdtd2d_desc *d, Plan2 &p)
         return ((d->nx + i - 1) / i) * ((d->ny + j - 1) / j);
     };
     p.vac = count(kFlat2) <= kFlatMaxTiles2 ? Tiles2::flat : Tiles2::tall;
+    p.thin = d->nx < kThinRows2 && count(kFlat2) > kThinTiles2;
     const Shape2 v = p.vac == Tiles2::flat ? kFlat2 : kTall2, q = kPlasma2;
     const int64_t vi = v.rows() - 2 * kSteps2, vj = v.cols() - 2 * kSteps2;
     const int64_t qi = q.rows() - 2 * kSteps2, qj = q.cols() - 2 * kSteps2;
@@ -198,7 +202,7 @@ void build_tiles2(const fdtd2d_desc *d, Plan2 &p)
     std::sort(by_row.begin(), by_row.end());
     p.tprobe.clear();
     p.row.assign(d->n_probes, 0);
-    p.rows = 0;
+    p.cell.clear();
     for (size_t n = 0; n < p.tiles.size(); ++n) {
         Tile2 &t = p.tiles[n];
         const Shape2 &sh = (int64_t)n < p.nplasma ? q : v;
@@ -221,12 +225,44 @@ void build_tiles2(const fdtd2d_desc *d, Plan2 &p)
                 p.tprobe.resize(p.tprobe.size() + 64, LaneProbes{0, 0});
             }
             LaneProbes &lp = p.tprobe[p.tprobe.size() - 64 + lane];
-            if (!lp.mask) lp.first = (int32_t)p.rows;
-            if (!((lp.mask >> bit) & 1)) ++p.rows;
+            const int64_t *pr = d->probes + 3 * in[k].second;
+            if (!lp.mask) lp.first = (int32_t)p.cell.size();
+            if (!((lp.mask >> bit) & 1)) p.cell.push_back((pr[0] * d->nx + pr[1]) * d->ny + pr[2]);
             lp.mask |= 1u << bit;
-            p.row[in[k].second] = (int32_t)(p.rows - 1);
+            p.row[in[k].second] = (int32_t)(p.cell.size() - 1);
         }
     }
+    p.rows = (int64_t)p.cell.size();
+}
+
+// The workspace, with one copy of the fields and currents or two.
+void lay_out2(const fdtd2d_desc *d, Plan2 &p, bool one)
+{
+    Lay &L = p.L;
+    L = Lay();
+    p.one = one;
+    for (int i = 0; i < (one ? 1 : 2); ++i) {
+        for (int c = 0; c < p.ncomp; ++c) p.o_E[i][c] = L.take(p.es * p.N);
+        for (int c = 0; c < p.nh; ++c) p.o_H[i][c] = L.take(p.es * p.N);
+        for (int c = 0; c < p.ncomp; ++c) p.o_J[i][c] = L.take(8 * p.S);
+    }
+    p.o_span = L.take(8 * d->nx);
+    p.o_rowoff = L.take(8 * d->nx);
+    for (int c = 0; c < p.ncomp; ++c) {
+        p.o_wp2[c] = L.take(8 * p.S);
+        p.o_nu[c] = L.take(8 * p.S);
+    }
+    const int P = std::max(d->n_probes, 1);
+    p.o_cell = L.take(8 * P);
+    p.o_freqs = L.take(8 * d->n_freqs);
+    p.o_samp = L.take(8 * (int64_t)P * kSB2);
+    p.o_X = L.take(16 * (int64_t)P * d->n_freqs);
+    p.o_Xtmp = L.take(16 * (int64_t)P * d->n_freqs);
+    p.o_tw = L.take(16 * (int64_t)std::min(kSB2, kTwiddleChunk) * d->n_freqs);
+    if (one) return;
+    p.o_tiles = L.take((int64_t)sizeof(Tile2) * (int64_t)p.tiles.size());
+    p.o_tprobe = L.take((int64_t)sizeof(LaneProbes) * (int64_t)p.tprobe.size());
+    p.o_srcv = L.take(8 * kSB2);
 }
 
 int plan2(const fdtd2d_desc *d, Plan2 &p)
@@ -257,28 +293,7 @@ int plan2(const fdtd2d_desc *d, Plan2 &p)
     }
     p.S = S;
     build_tiles2(d, p);
-    Lay &L = p.L;
-    L = Lay();
-    for (int i = 0; i < 2; ++i) {
-        for (int c = 0; c < p.ncomp; ++c) p.o_E[i][c] = L.take(p.es * p.N);
-        for (int c = 0; c < p.nh; ++c) p.o_H[i][c] = L.take(p.es * p.N);
-        for (int c = 0; c < p.ncomp; ++c) p.o_J[i][c] = L.take(8 * S);
-    }
-    p.o_span = L.take(8 * d->nx);
-    p.o_rowoff = L.take(8 * d->nx);
-    for (int c = 0; c < p.ncomp; ++c) {
-        p.o_wp2[c] = L.take(8 * S);
-        p.o_nu[c] = L.take(8 * S);
-    }
-    const int P = std::max(d->n_probes, 1);
-    p.o_tiles = L.take((int64_t)sizeof(Tile2) * (int64_t)p.tiles.size());
-    p.o_tprobe = L.take((int64_t)sizeof(LaneProbes) * (int64_t)p.tprobe.size());
-    p.o_srcv = L.take(8 * kSB2);
-    p.o_freqs = L.take(8 * d->n_freqs);
-    p.o_samp = L.take(8 * (int64_t)P * kSB2);
-    p.o_X = L.take(16 * (int64_t)P * d->n_freqs);
-    p.o_Xtmp = L.take(16 * (int64_t)P * d->n_freqs);
-    p.o_tw = L.take(16 * (int64_t)std::min(kSB2, kTwiddleChunk) * d->n_freqs);
+    lay_out2(d, p, p.thin);
     return FDTD_OK;
 }
 
@@ -295,6 +310,7 @@ struct fdtd2d {
     double *J[2][2] = {};
     int cur = 0;                             // the copy that holds the state
     Tile2 *tiles = nullptr;
+    int64_t *cells = nullptr;                // cells of the sample rows
     double *freqs = nullptr, *samp = nullptr, *srcv = nullptr;
     double2 *X = nullptr, *Xtmp = nullptr, *tw = nullptr;
     int64_t steps = 0, win_base = 0;
@@ -358,6 +374,15 @@ Fields2<T> copy2(const fdtd2d *h, int i)
     return f;
 }
 
+// k steps taken: fold the sample window if it is full.
+void took2(fdtd2d *h, int k)
+{
+    h->steps += k;
+    if (h->steps - h->win_base < kSB2) return;
+    fold(h, h->X);
+    h->win_base = h->steps;
+}
+
 // The side stream starts behind the handle's (fork), which goes on behind it (join).
 hipError_t fork2(fdtd2d *h)
 {
@@ -370,14 +395,28 @@ hipError_t join2(fdtd2d *h)
     return e == hipSuccess ? hipStreamWaitEvent(h->stream, h->ev_join, 0) : e;
 }
 
+// Whether k <= kSteps2 steps are taken as one pass of tiles (else one by one, in
+// place): internal2d.h says what both cost.
+bool by_pass(const fdtd2d *h, int64_t k)
+{
+    return !h->p.one && (k > 2 || (k == 2 && h->p.N > kTwoStepsBelow2));
+}
+
 template <typename T>
 hipError_t advance2_t(fdtd2d *h, int64_t n)
 {
     hipError_t e = hipSuccess;
     while (n > 0) {
         const int slot = (int)(h->steps - h->win_base);
-        if (slot == 0 && h->g.has_src) launch_src2d(h->g, h->steps + 1, kSB2, h->srcv, h->stream);
+        if (slot == 0 && h->g.has_src && !h->p.one) launch_src2d(h->g, h->steps + 1, kSB2, h->srcv, h->stream);
         const int k = (int)std::min<int64_t>(std::min<int64_t>(n, kSteps2), kSB2 - slot);
+        if (!by_pass(h, k)) {
+            for (int s = 0; s < k; ++s)
+                launch_step2d<T>(h->g, copy2<T>(h, h->cur), h->cells, h->p.rows, h->steps + s + 1, slot + s, h->stream);
+            took2(h, k);
+            n -= k;
+            continue;
+        }
         const Fields2<T> in = copy2<T>(h, h->cur), out = copy2<T>(h, h->cur ^ 1);
         // plasma and vacuum tiles write disjoint cells: side by side
         const int64_t nvac = (int64_t)h->p.tiles.size() - h->p.nplasma;
@@ -393,12 +432,8 @@ hipError_t advance2_t(fdtd2d *h, int64_t n)
             return e;
         }
         h->cur ^= 1;
-        h->steps += k;
+        took2(h, k);
         n -= k;
-        if (h->steps - h->win_base == kSB2) {
-            fold(h, h->X);
-            h->win_base = h->steps;
-        }
     }
     return hipGetLastError();
 }
@@ -445,6 +480,8 @@ int fdtd2d_create(const fdtd2d_desc *desc, void *workspace, size_t bytes, fdtd2d
         return rc;
     }
     Plan2 &p = h->p;
+    // a buffer too small for two copies of the fields holds one
+    if (workspace && bytes < (size_t)p.L.total) lay_out2(desc, p, true);
     if (workspace && (bytes < (size_t)p.L.total || ((uintptr_t)workspace % kAlign2))) {
         delete h;
         return fail2(FDTD_E_WORKSPACE, "workspace of %zu bytes (needs %lld, %lld-byte aligned)", bytes,
@@ -456,6 +493,11 @@ int fdtd2d_create(const fdtd2d_desc *desc, void *workspace, size_t bytes, fdtd2d
         h->ws = (char *)workspace;
     } else {
         hipError_t e = hipMalloc((void **)&h->ws, (size_t)p.L.total);
+        if (e != hipSuccess && !p.one) {
+            (void)hipGetLastError();
+            lay_out2(desc, p, true);
+            e = hipMalloc((void **)&h->ws, (size_t)p.L.total);
+        }
         if (e != hipSuccess) {
             delete h;
             return fail2(FDTD_E_DEVICE, "hipMalloc(%lld) failed: %s", (long long)p.L.total, hipGetErrorString(e));
@@ -481,11 +523,13 @@ int fdtd2d_create(const fdtd2d_desc *desc, void *workspace, size_t bytes, fdtd2d
         g.wp2[c] = (const double *)(w + p.o_wp2[ce]);
         g.nu[c] = (const double *)(w + p.o_nu[ce]);
         for (int i = 0; i < 2; ++i) {
-            h->E[i][c] = w + p.o_E[i][ce];
-            h->H[i][c] = w + p.o_H[i][ch];
-            h->J[i][c] = (double *)(w + p.o_J[i][ce]);
+            const int k = p.one ? 0 : i;
+            h->E[i][c] = w + p.o_E[k][ce];
+            h->H[i][c] = w + p.o_H[k][ch];
+            h->J[i][c] = (double *)(w + p.o_J[k][ce]);
         }
     }
+    h->cells = (int64_t *)(w + p.o_cell);
     h->tiles = (Tile2 *)(w + p.o_tiles);
     h->srcv = (double *)(w + p.o_srcv);
     g.srcv = h->srcv;
@@ -526,17 +570,20 @@ int fdtd2d_create(const fdtd2d_desc *desc, void *workspace, size_t bytes, fdtd2d
         H2D(w + p.o_wp2[c], cw.data() + c * p.S, 8 * p.S);
         H2D(w + p.o_nu[c], cn.data() + c * p.S, 8 * p.S);
     }
-    H2D(h->tiles, p.tiles.data(), sizeof(Tile2) * p.tiles.size());
-    H2D(w + p.o_tprobe, p.tprobe.data(), sizeof(LaneProbes) * p.tprobe.size());
+    H2D(h->cells, p.cell.data(), 8 * p.cell.size());
+    if (!p.one) {
+        H2D(h->tiles, p.tiles.data(), sizeof(Tile2) * p.tiles.size());
+        H2D(w + p.o_tprobe, p.tprobe.data(), sizeof(LaneProbes) * p.tprobe.size());
+    }
     H2D(w + p.o_freqs, desc->freqs_hz, 8 * (size_t)desc->n_freqs);
     // the legacy null stream takes every launch itself
-    if (e == hipSuccess && st && p.nplasma > 0 && p.nplasma < (int64_t)p.tiles.size()) {
+    if (e == hipSuccess && st && !p.one && p.nplasma > 0 && p.nplasma < (int64_t)p.tiles.size()) {
         e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming);
     }
     if (e == hipSuccess) {
-        launch_src2d(g, 1, kSB2, h->srcv, st);   // tiles read the table also without a source
+        if (!p.one) launch_src2d(g, 1, kSB2, h->srcv, st);   // tiles read the table also without a source
         reset2(h);
         e = hipStreamSynchronize(st);
     }
@@ -611,9 +658,10 @@ int fdtd2d_run(fdtd2d *h, int64_t nsteps)
     } else {
         h->steps = nsteps;
         h->win_base = nsteps / kSB2 * kSB2;
-        // passes of the captured run: kSteps2 steps each, cut at window ends
+        // passes of the captured run: kSteps2 steps each (windows hold whole
+        // passes), then the rest
         static_assert(kSB2 % kSteps2 == 0, "windows hold whole passes");
-        h->cur = (int)(((nsteps + kSteps2 - 1) / kSteps2) & 1);
+        h->cur = (int)((by_pass(h, kSteps2) * (nsteps / kSteps2) + by_pass(h, nsteps % kSteps2)) & 1);
     }
     e = hipGraphLaunch(it->second, h->stream);
     if (e != hipSuccess) return not_run(fail2(FDTD_E_DEVICE, "graph launch failed: %s", hipGetErrorString(e)));

@@ -78,6 +78,14 @@ struct Shape2 {
 // TE FP64 512^2 2.8 against 3.6, 1000^2 5.0 against 4.5, 4096^2 43 against 36.
 constexpr Shape2 kFlat2 = {4, 2, 8}, kTall2 = {6, 2, 8};
 constexpr int64_t kFlatMaxTiles2 = 512;      // two workgroups on each of 256 CUs
+// Steps taken one by one in place instead of as a pass of tiles.  One step
+// alone: a pass costs its loads and stores however few steps it takes (4096^2 TM
+// FP32 157 us against 116, 1000^2 TE FP32 42 against 17), and on small grids so do two (256^2 29
+// against 24 us; 1000^2 39 against 35; 4096^2 165 against 232).  All steps: grids of two or three
+// rows, of which a tile's sixteen output rows leave most empty, where the tiles fill the GPU
+// (2 x 2^20 cells 43 us a step against 29; 4 x 2^18 13 against 12.5, 2 x 4096 1.8 against 5.9).
+constexpr int64_t kTwoStepsBelow2 = 1 << 20; // cells
+constexpr int64_t kThinRows2 = 4, kThinTiles2 = 1024;
 // Plasma tiles hold six coefficients and a current a cell and component, so
 // one column a lane and four rows a wave.
 constexpr Shape2 kPlasma2 = {4, 1, 12};
@@ -88,6 +96,11 @@ enum class Tiles2 { flat, tall, plasma };
 template <typename T>
 void launch_tiles2d(const Grid2 &g, const Fields2<T> &in, const Fields2<T> &out, const Tile2 *tiles,
                     int64_t ntiles, Tiles2 shape, int nsteps, int slot0, hipStream_t st);
+
+// Step m in place, the sample rows' cells (component N + cell each) into `slot`.
+template <typename T>
+void launch_step2d(const Grid2 &g, const Fields2<T> &f, const int64_t *cells, int64_t rows, int64_t m, int slot,
+                   hipStream_t st);
 
 // The source values of steps m_first .. m_first + count - 1.
 void launch_src2d(const Grid2 &g, int64_t m_first, int count, double *srcv, hipStream_t st);

@@ -53,11 +53,16 @@ class FdtdPlasma2D:
         n = ctypes.c_size_t()
         L.check2(L.lib().fdtd2d_workspace_bytes(ctypes.byref(d), ctypes.byref(n)))
         self.workspace_bytes = n.value
-        with torch.cuda.stream(self.stream):
-            self.workspace = torch.empty(max(1, n.value), dtype=torch.uint8, device=self.device)
+        try:
+            with torch.cuda.stream(self.stream):
+                self.workspace = torch.empty(max(1, n.value), dtype=torch.uint8, device=self.device)
+        except torch.cuda.OutOfMemoryError:
+            # the library then allocates what fits: one copy of the fields instead of two
+            self.workspace = None
+            torch.cuda.empty_cache()
         h = ctypes.c_void_p()
-        L.check2(L.lib().fdtd2d_create(ctypes.byref(d), ctypes.c_void_p(self.workspace.data_ptr()), n.value,
-                                       ctypes.byref(h)))
+        at = None if self.workspace is None else ctypes.c_void_p(self.workspace.data_ptr())
+        L.check2(L.lib().fdtd2d_create(ctypes.byref(d), at, n.value, ctypes.byref(h)))
         self.h = h
 
     def step(self, nsteps: int) -> "FdtdPlasma2D":

@@ -21,6 +21,7 @@ Captured capture;
 std::set<void *> recorded;         // events recorded in the capture in progress
 std::string fails;                 // the next call of this name fails
 int misuses = 0;
+long limit = 0;                    // the most bytes of one allocation (0: any)
 long launches = 0, bad_grids = 0, waits = 0;
 
 bool failing(const char *what)
@@ -48,6 +49,7 @@ hipError_t drop(std::set<void *> &from, void *what)
 }  // namespace
 
 extern "C" {
+void stub_limit(long bytes) { limit = bytes; }
 void stub_fail(const char *what) { fails = what; }
 int stub_misuses() { return misuses; }
 int stub_live() { return (int)(streams.size() + events.size() + graphs.size() + execs.size()); }
@@ -55,7 +57,11 @@ long stub_waits() { return waits; }
 long stub_launches() { return launches; }
 long stub_bad_grids() { return bad_grids; }
 
-hipError_t hipMalloc(void **p, size_t n) { *p = malloc(n + 256); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipMalloc(void **p, size_t n)
+{
+    *p = limit && (long)n > limit ? nullptr : malloc(n + 256);
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
 hipError_t hipFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }

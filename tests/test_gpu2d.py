@@ -144,6 +144,75 @@ def test_2d_dense_probes_match_fields(G, mode, nx, ny, px, py):
         assert rel(X, ref) <= (1e-12 if prec == "f64" else 2e-5), prec
 
 
+class OneCopy:
+    """The smallest workspace the library takes for p, through the C ABI."""
+
+    def __init__(self, G, p, precision):
+        import ctypes
+        import re
+        import torch
+        from paper_1709_00821_amd import _lib as L
+        st = torch.cuda.Stream()
+        self.d, self.keep = G.make_desc2(p, precision, st.cuda_stream)
+        self.p, self.st, self.L, h = p, st, L.lib(), ctypes.c_void_p()
+        full = ctypes.c_size_t()
+        assert self.L.fdtd2d_workspace_bytes(ctypes.byref(self.d), ctypes.byref(full)) == 0
+        self.ws = torch.empty(full.value, dtype=torch.uint8, device="cuda")
+        at = ctypes.c_void_p(self.ws.data_ptr())
+        assert self.L.fdtd2d_create(ctypes.byref(self.d), at, 256, ctypes.byref(h)) == L.E_WORKSPACE
+        need = int(re.search(rb"needs (\d+)", self.L.fdtd2d_last_error()).group(1))
+        self.need, self.full = need, full.value
+        assert self.L.fdtd2d_create(ctypes.byref(self.d), at, need - 1, ctypes.byref(h)) == L.E_WORKSPACE
+        assert self.L.fdtd2d_create(ctypes.byref(self.d), at, need, ctypes.byref(h)) == 0
+        self.h, self.problem, self.desc = h, p, self.d
+
+    def result(self, G):
+        f = G.FdtdPlasma2D
+        return f.spectra(self), f.fields(self)
+
+
+@pytest.mark.parametrize("mode,nx,ny,px,py", [("tm", 70, 90, False, False), ("te", 33, 200, True, False),
+                                              ("te", 64, 48, False, True), ("tm", 3, 140000, True, False),
+                                              ("te", 2, 131100, False, True)])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_2d_in_place_steps_bitwise(G, mode, nx, ny, px, py, prec):
+    """Steps taken one by one in place (a workspace that holds one copy of the
+    fields, grids of two or three rows, the odd steps of any composition) against
+    passes of tiles: the same spectra and fields, and the oracle's."""
+    rng = np.random.default_rng(nx + ny)
+    wide = nx < 4
+    p = W.random_2d(rng, mode, max(nx, 4), ny if not wide else 400, periodic_x=px, periodic_y=py)
+    if wide:                                  # the long way round: the random grid's rows, then vacuum
+        w, v = np.zeros((p.ncomp, nx, ny)), np.full((p.ncomp, nx, ny), 1e10)
+        w[:, :, 100:500], v[:, :, 100:500] = p.wp2[:, :nx], p.nu[:, :nx]
+        pr = p.probes.copy()
+        pr[:, 1], pr[:, 2] = pr[:, 1] % nx, 100 + pr[:, 2]
+        p = p.copy(nx=nx, ny=ny, wp2=w, nu=v, probes=pr, src=(nx - 1, 300))
+    say(f"case 2d in place {mode} {nx}x{ny} {prec}")
+    T = 45
+    one = OneCopy(G, p, prec)
+    assert one.need < one.full or wide
+    L = one.L
+    assert L.fdtd2d_run(one.h, 19) == 0 and L.fdtd2d_run(one.h, T) == 0      # captured, in place
+    X1, F1 = one.result(G)
+    assert L.fdtd2d_run(one.h, 19) == 0 and L.fdtd2d_step(one.h, T - 19) == 0
+    X2, F2 = one.result(G)
+    assert L.fdtd2d_destroy(one.h) == 0
+    with G.FdtdPlasma2D(p, precision=prec) as h:
+        h.run(T)
+        Xa, Fa = h.spectra(), h.fields()
+        h.run(9)                              # one pass, one step in place
+        h.run(10).run(9).step(1).step(2).step(3).step(1).step(T - 16)
+        Xb, Fb = h.spectra(), h.fields()
+    for X, F in ((X2, F2), (Xa, Fa), (Xb, Fb)):
+        assert np.array_equal(X1, X)
+        for k in ("E", "H", "J"):
+            assert np.array_equal(F1[k], F[k]), k
+    o = oracle.run2d(p, T, kind="omp")
+    tol = 1e-12 if prec == "f64" else 2e-5
+    assert rel(Xa, o["X"]) <= tol and max(errs(Fa, o)) <= 10 * tol
+
+
 def test_2d_step_composition_and_replay(G):
     p = W.random_2d(np.random.default_rng(5), "te", 70, 90)
     say("case 2d step composition")

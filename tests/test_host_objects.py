@@ -92,6 +92,37 @@ for make, step, err, destroy in ((long_1d, lib.fdtd_plasma_step, lib.fdtd_plasma
 """
 
 
+SIZES = CHILD + r"""
+rng = np.random.default_rng(1)
+up = lambda b: (max(b, 16) + 255) // 256 * 256
+for mode, nx, ny, prec, P, F in (("tm", 40, 50, "f32", 0, 1), ("te", 300, 310, "f64", 9, 64), ("te", 64, 2000, "f32", 4096, 3),
+                                 ("tm", 2, 200000, "f64", 2, 16)):
+    wp2 = np.zeros((1 if mode == "tm" else 2, nx, ny))
+    wp2[:, nx // 3:nx // 2 + 1, 5:ny // 2] = 1e21
+    nc, nh, es = len(wp2), 3 - len(wp2), 8 if prec == "f64" else 4
+    S = int(np.any(wp2 > 0, axis=0).sum())
+    p = W.Problem2D(mode=mode, nx=nx, ny=ny, d=75e-6, dt=1e-13, wp2=wp2, nu=wp2 * 0, src=(1, 1), src_tau=1e-12, src_t0=1e-12,
+                    src_amp=1.0, probes=np.stack([rng.integers(0, k, P) for k in (nc, nx, ny)], axis=1), freqs=np.arange(1.0, F + 1))
+    d, keep = make_desc2(p, prec, STREAM)
+    # one copy of the fields and currents, the plasma, the probes, their window, spectra and twiddles
+    enough = ((nc + nh) * up(es * nx * ny) + 2 * up(8 * nx) + 3 * nc * up(8 * S) + up(24 * max(P, 1)) + up(8 * F) +
+              up(8 * max(P, 1) * 2048) + 2 * up(16 * max(P, 1) * F) + up(16 * 1024 * F))
+    mem = (ctypes.c_char * (enough + 256))()
+    at = (ctypes.addressof(mem) + 255) // 256 * 256
+    h = ctypes.c_void_p()
+    assert lib.fdtd2d_create(ctypes.byref(d), ctypes.c_void_p(at), enough, ctypes.byref(h)) == 0, lib.fdtd2d_last_error()
+    assert lib.fdtd2d_run(h, 40) == 0 and lib.fdtd2d_step(h, 9) == 0
+    lib.fdtd2d_destroy(h)
+    full = ctypes.c_size_t()
+    assert lib.fdtd2d_workspace_bytes(ctypes.byref(d), ctypes.byref(full)) == 0
+    stub.stub_limit(ctypes.c_long(full.value - 1))     # a card one byte short of two copies
+    assert lib.fdtd2d_create(ctypes.byref(d), None, 0, ctypes.byref(h)) == (0 if nx > 3 else L.E_DEVICE)
+    stub.stub_limit(ctypes.c_long(0))
+    if h: lib.fdtd2d_destroy(h)
+assert stub.stub_misuses() == 0 and stub.stub_bad_grids() == 0
+"""
+
+
 @pytest.fixture(scope="module")
 def stub(tmp_path_factory):
     so = tmp_path_factory.mktemp("stub") / "hip_stub.so"
@@ -122,3 +153,7 @@ def test_a_run_that_was_not_captured_leaves_the_state(stub, what):
 @pytest.mark.parametrize("what", ["hipEventRecord", "hipStreamWaitEvent"])
 def test_a_step_whose_streams_did_not_wait_is_reported(stub, what):
     child(EVENTS, stub, what)
+
+
+def test_2d_takes_a_workspace_of_one_copy_of_the_fields(stub):
+    child(SIZES, stub)

@@ -124,6 +124,7 @@ struct fdtd_plasma {
     bool spans[2] = {false, false};   // class 0, 1 holds spans
     Group *d_segs = nullptr;   // segments (CPML and role nodes, or every node of a short grid)
     int64_t nseg = 0, seg_nodes = 0;
+    int seg_waves = 1;
 
     // resident executor
     Group *d_slots = nullptr;
@@ -353,6 +354,7 @@ struct Plan {
     std::vector<Group> segs;    // segments of the tiled executor
     bool spans[2] = {false, false};   // class 0, 1 holds spans
     int64_t nseg = 0, seg_nodes = 0;
+    int seg_waves = 1;        // of the longest segment
     int exec = 0, tileC = 8, Kh = 16, tileW = 1, resC = 8, resWaves = 8;
     int wideC = 0;            // wide vacuum tiles: 64 wideC nodes (0: none)
 };
@@ -516,9 +518,9 @@ void push_group(const fdtd_plasma_desc *d, std::vector<Group> &groups, int C, in
         }
         const bool left = s.lo == 0, right = hi == n;
         GroupRole r = kResPlain;
-        if (probes > 2 || (left && right) || ((left || right) && d->bc == FDTD_BC_PEC) ||
-            (right && s.lo + 64LL * C != n))
-            r = kResGeneral;
+        if (probes > 2) r = kResGeneral;
+        else if ((left && right) || ((left || right) && d->bc == FDTD_BC_PEC) || (right && s.lo + 64LL * C != n))
+            r = kResEnds;
         else if (left) r = kResLeft;
         else if (right) r = kResRight;
         else if (probes > 0 || (d->src_cell[b] >= s.lo && d->src_cell[b] < hi)) r = kResInner;
@@ -620,6 +622,7 @@ void build_segments(const fdtd_plasma_desc *d, Plan &p)
             push_group(d, p.segs, kSegC, b, first[b], std::max<int64_t>(0, std::min(x - p.Kh, held)), x1, x, e);
             ++p.nseg;
             p.seg_nodes += e - x;
+            p.seg_waves = std::max(p.seg_waves, (int)p.segs.back().nwaves);
         }
     }
     if (!groups_hold_cpml(d, p.segs, kSegC)) {
@@ -1050,7 +1053,7 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
             const bool fork = h->side && (h->ntiles[2] || h->ntiles[3] || h->nseg) && !h->profiling;
             auto segments = [&](hipStream_t st) {
                 if (h->nseg)
-                    launch_group<T>(g, s, h->cur, h->cur ^ 1, h->d_segs, h->nseg, kSegWaves, kSegC, (int)k, slot, st);
+                    launch_group<T>(g, s, h->cur, h->cur ^ 1, h->d_segs, h->nseg, h->seg_waves, kSegC, (int)k, slot, st);
             };
             auto on_side = [&](int c) { return fork && c >= 2; };
             if (fork) {
@@ -1338,6 +1341,7 @@ int create_impl(const fdtd_plasma_desc *desc, Plan &p, void *dev_workspace, size
     h->d_slots = (Group *)(w + p.o_slots);
     h->d_segs = (Group *)(w + p.o_segs);
     h->nseg = p.nseg;
+    h->seg_waves = p.seg_waves;
     for (int c = 0; c < 2; ++c) h->spans[c] = p.spans[c];
     h->seg_nodes = p.seg_nodes;
 

@@ -412,7 +412,7 @@ __device__ __forceinline__ void group_wave(const Grids &g, const State<T> &s, in
 {
     typedef Chunk<T, C, PLASMA, CPML> K;
     typedef typename K::R R;
-    constexpr bool GENERAL = ROLE == kResGeneral;
+    constexpr bool GENERAL = ROLE == kResGeneral, ENDS = ROLE == kResEnds || GENERAL;
     const int b = gr.grid;
     const int64_t off = g.off[b], n = g.n[b];
     const bool has_l = wv.left, has_r = wv.right;
@@ -443,7 +443,7 @@ __device__ __forceinline__ void group_wave(const Grids &g, const State<T> &s, in
     if constexpr (ROLE != kResPlain) {
         role = wave_role<C>(g, b, n, wv.lo, hold_hi);
         wp = wave_probes_find<C>(g, b, wv.lo, st_lo, st_hi);
-        ends_init<R, C, !GENERAL>(ck.E, role, ends);
+        ends_init<R, C, !ENDS>(ck.E, role, ends);
         // the two waves that may hold the source: the one that owns its node,
         // and a neighbour in its halo
         const int64_t sn = g.src[b];
@@ -491,23 +491,21 @@ __device__ __forceinline__ void group_wave(const Grids &g, const State<T> &s, in
             ends.eR = v;
             ends.eR1 = en1;
             ck.E[C - 1] = lane == 63 ? v : ck.E[C - 1];
-        } else if constexpr (GENERAL) {
-            if (role.left_lane >= 0) {
-                const R v = mur ? (R)(ends.e1 + (R)g.cm * (ck.E[1] - ends.e0)) : (R)0;
-                ends.e1 = ck.E[1];
-                ends.e0 = v;
-                ck.E[0] = lane == 0 ? v : ck.E[0];
-            }
-            if (role.right_lane >= 0) {
-                const int ir = role.right_reg;
-                const R prev = shfl_up1(ck.E[C - 1]);
-                const R left1 = upick<R, C>(ck.E, ir > 0 ? ir - 1 : 0);
-                const R en1 = ir > 0 ? left1 : prev;
-                const R v = mur ? (R)(ends.eR1 + (R)g.cm * (en1 - ends.eR)) : (R)0;
-                uput<R, C>(ck.E, ir, lane == role.right_lane, v);
-                ends.eR = v;
-                ends.eR1 = en1;
-            }
+        } else if constexpr (ENDS) {                // either end or both, without a branch
+            const R vl = mur ? (R)(ends.e1 + (R)g.cm * (ck.E[1] - ends.e0)) : (R)0;
+            ends.e1 = ck.E[1];
+            ends.e0 = vl;
+            const R prev = shfl_up1(ck.E[C - 1]);
+            R en1 = prev;
+#pragma unroll
+            for (int i = 1; i < C; ++i) en1 = role.right_reg == i ? ck.E[i - 1] : en1;
+            const R vr = mur ? (R)(ends.eR1 + (R)g.cm * (en1 - ends.eR)) : (R)0;
+            ends.eR = vr;
+            ends.eR1 = en1;
+            ck.E[0] = lane == role.left_lane ? vl : ck.E[0];
+            uput<R, C>(ck.E, role.right_reg, lane == role.right_lane, vr);
+        }
+        if constexpr (GENERAL) {
             if (wp.n > 0) wave_probes<R, C>(g, b, wv.lo, st_lo, st_hi, lane, ck.E, slot0 + st);
         }
         if constexpr (ROLE != kResPlain && !GENERAL) {
@@ -624,6 +622,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_group(Grids g, State<T> s, int c
         case kResInner: FDTDP_WAVE(true, false, kResInner); break;
         case kResLeft: FDTDP_WAVE(true, false, kResLeft); break;
         case kResRight: FDTDP_WAVE(true, false, kResRight); break;
+        case kResEnds: FDTDP_WAVE(true, false, kResEnds); break;
         default: FDTDP_WAVE(true, false, kResGeneral); break;
         }
     } else {
@@ -632,6 +631,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_group(Grids g, State<T> s, int c
         case kResInner: FDTDP_WAVE(false, false, kResInner); break;
         case kResLeft: FDTDP_WAVE(false, false, kResLeft); break;
         case kResRight: FDTDP_WAVE(false, false, kResRight); break;
+        case kResEnds: FDTDP_WAVE(false, false, kResEnds); break;
         default: FDTDP_WAVE(false, false, kResGeneral); break;
         }
     }

@@ -486,6 +486,33 @@ def test_group_waves_bitwise(G, n, bc, cpml):
                 assert np.array_equal(F[0][k], Fs[0][k]), (ex, kw, k)
 
 
+@pytest.mark.parametrize("bc", ["mur", "pec"])
+@pytest.mark.parametrize("ns", [(3, 4, 5), (6, 7, 97), (126, 127, 128), (129, 223, 224)])
+def test_group_of_one_wave_bitwise(G, ns, bc):
+    """Grids that one wave holds, both ends in it, node n - 1 in either register,
+    with one, two and nine probes, alone and 300 in a batch (segments), resident
+    and with 500-node neighbours, against the per-step path, bit for bit."""
+    rng = np.random.default_rng(sum(ns))
+    T = 131
+    say(f"case group of one wave {ns} {bc}")
+    for P in (1, 2, 9):
+        probs = []
+        for n in ns + (500,):
+            p = W.random_slab(rng, max(n, 6), bc=bc, n_freqs=4)
+            probes = rng.integers(0, n, P)
+            probes[:2] = (0, n - 1)[:P]
+            probs.append(p.copy(n=n, wp2=np.where(np.arange(n) % (n - 1) > 0, p.wp2[:n], 0.0), nu=p.nu[:n],
+                                src_cell=int(rng.integers(1, n - 1)), probes=probes, freqs=np.linspace(0, 6e10, 4)))
+        Xs, Fs = gpu_run(G, probs, T, exec="step")
+        for ex, prs in (("auto", probs), ("resident", probs), ("tiled", probs), ("auto", probs[:3]),
+                        ("auto", probs[:3] * 100)):
+            X, F = gpu_run(G, prs, T, exec=ex)
+            for b in range(4 if prs is probs else 3):
+                assert np.array_equal(X[b], Xs[b]), (ex, P, b)
+                for k in ("E", "H", "J"):
+                    assert np.array_equal(F[b][k], Fs[b][k]), (ex, P, b, k)
+
+
 @pytest.mark.parametrize("prec,K", [("f64", 64), ("f64", 52), ("f32", 60)])
 def test_spans_bitwise(G, prec, K):
     """Three long plasma grids whose tiles become spans of up to four waves, with

@@ -531,17 +531,16 @@ void push_group(const fdtd_plasma_desc *d, std::vector<Group> &groups, int C, in
     groups.push_back(gr);
 }
 
-// Whether the groups' waves can hold the CPML layers: each layer in the own
-// nodes of the one wave at its grid end (no psi is exchanged), and, above two
-// nodes a lane, no plasma in that wave (the register file).
-bool groups_hold_cpml(const fdtd_plasma_desc *d, const std::vector<Group> &groups, int C)
+// Whether the waves of groups of kCpmlC nodes a lane can hold the CPML layers:
+// each layer in the own nodes of the one wave at its grid end (no psi is
+// exchanged).
+bool groups_hold_cpml(const fdtd_plasma_desc *d, const std::vector<Group> &groups)
 {
     for (const Group &gr : groups)
         for (int w = 0; w < gr.nwaves; ++w) {
             if (!((gr.cpml >> w) & 1)) continue;
-            const GroupWave s = group_wave_at(gr, w, C);
+            const GroupWave s = group_wave_at(gr, w, kCpmlC);
             const int64_t n = d->cells[gr.grid], P = d->cpml_cells;
-            if (C > 2 && ((gr.plasma >> w) & 1)) return false;
             const bool left = s.own_lo == 0, right = s.own_hi == n;
             if (!left && !right) return false;                        // a layer in an inner wave
             if (left && s.right && P + 1 > s.own_hi - kGroupHalo) return false;
@@ -625,7 +624,7 @@ void build_segments(const fdtd_plasma_desc *d, Plan &p)
             p.seg_waves = std::max(p.seg_waves, (int)p.segs.back().nwaves);
         }
     }
-    if (!groups_hold_cpml(d, p.segs, kSegC)) {
+    if (!groups_hold_cpml(d, p.segs)) {
         p.segs.clear();
         p.nseg = p.seg_nodes = 0;
         return;
@@ -757,8 +756,9 @@ int plan(const fdtd_plasma_desc *d, Plan &p)
         if (d->precision == FDTD_F32 && d->bc != FDTD_BC_CPML && d->batch <= kResidentAutoGrids &&
             longest + 1 <= kResMaxNodes)
             p.exec = FDTD_EXEC_RESIDENT;
+        // (grids of up to that length take the shape that holds layers)
         if (d->precision == FDTD_F64 && longest <= resident_auto64(d))
-            p.exec = build_bins(d, p) && groups_hold_cpml(d, p.slots, p.resC) ? FDTD_EXEC_RESIDENT : FDTD_EXEC_TILED;
+            p.exec = build_bins(d, p) && groups_hold_cpml(d, p.slots) ? FDTD_EXEC_RESIDENT : FDTD_EXEC_TILED;
     }
     if (p.exec == FDTD_EXEC_RESIDENT) {
         if (!build_bins(d, p))

@@ -605,18 +605,22 @@ __global__ __launch_bounds__(WAVES * 64) void k_group(Grids g, State<T> s, int c
     const int role = (w < 10 ? gr.role[0] >> (3 * w) : gr.role[1] >> (3 * (w - 10))) & 7;
 #define FDTDP_WAVE(PLASMA, CPML, ROLE) \
     group_wave<T, C, WAVES, PLASMA, CPML, ROLE>(g, s, cur, out, gr, wv, lds, w, lane, nsteps, slot0)
-    if ((gr.cpml >> w) & 1) {
-        // plasma beside a layer: at two nodes a lane only (the register file)
-        if (C == 2 && ((gr.plasma >> w) & 1)) {
-            FDTDP_WAVE(C == 2, true, kResGeneral);
-        } else {
-            switch (role) {
-            case kResLeft: FDTDP_WAVE(false, true, kResLeft); break;
-            case kResRight: FDTDP_WAVE(false, true, kResRight); break;
-            default: FDTDP_WAVE(false, true, kResGeneral); break;
+    // layers at two nodes a lane only (kCpmlC; the register file)
+    if constexpr (C == kCpmlC) {
+        if ((gr.cpml >> w) & 1) {
+            if ((gr.plasma >> w) & 1) {
+                FDTDP_WAVE(true, true, kResGeneral);
+            } else {
+                switch (role) {
+                case kResLeft: FDTDP_WAVE(false, true, kResLeft); break;
+                case kResRight: FDTDP_WAVE(false, true, kResRight); break;
+                default: FDTDP_WAVE(false, true, kResGeneral); break;
+                }
             }
+            return;
         }
-    } else if ((gr.plasma >> w) & 1) {
+    }
+    if ((gr.plasma >> w) & 1) {
         switch (role) {
         case kResPlain: FDTDP_WAVE(true, false, kResPlain); break;
         case kResInner: FDTDP_WAVE(true, false, kResInner); break;

@@ -127,6 +127,9 @@ constexpr GroupShape kGroupShapes[3] = {{2, 16}, {4, 16}, {6, 12}};
 // The longest grid the resident executor takes.
 constexpr int64_t kResMaxNodes = 4096;
 static_assert(kGroupShapes[2].nodes() >= kResMaxNodes, "the widest shape holds the longest grid");
+// The shape whose waves may hold CPML layers.  The resident executor takes
+// such grids by AUTO alone, in FP64 and up to this shape's nodes.
+constexpr int kCpmlC = kGroupShapes[0].C;
 // Segments of a grid (the tiled executor's CPML and role tiles, or all of a
 // short grid): two nodes a lane, eight waves, so at most two waves share a SIMD
 // and a wave with a grid end, the source or probes still sets the pace. A
@@ -134,6 +137,7 @@ static_assert(kGroupShapes[2].nodes() >= kResMaxNodes, "the widest shape holds t
 // then spread over the SIMDs, not all on the first (700 grids of 20 to 128
 // nodes, 4096 steps FP32: 4.6 -> 1.5 ms with the step above).
 constexpr int kSegC = 2, kSegWaves = 8;
+static_assert(kSegC == kCpmlC, "segments hold layers");
 constexpr int64_t kSegNodes = kSegWaves * (64 * kSegC - 2 * kGroupHalo) + 2 * kGroupHalo;
 
 // AUTO picks the resident executor for FP32 storage on at most this many grids

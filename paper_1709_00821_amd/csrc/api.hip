@@ -13,6 +13,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -128,6 +129,7 @@ struct fdtd_plasma {
 
     // resident executor
     Group *d_slots = nullptr;
+    int32_t *d_bins = nullptr;
     int64_t nbins = 0;
     int resC = 8, resWaves = 8;
 
@@ -336,7 +338,7 @@ struct Plan {
     int64_t o_off = 0, o_n = 0, o_src = 0, o_probe = 0, o_wp2 = 0, o_nu = 0, o_freqs = 0, o_samp = 0, o_srcv = 0,
             o_X = 0, o_Xtmp = 0, o_tw = 0, o_cpml = 0;
     int64_t o_E[2] = {0, 0}, o_H[2] = {0, 0}, o_J[2] = {0, 0}, o_psiE[2] = {0, 0}, o_psiH[2] = {0, 0};
-    int64_t o_tiles = 0, o_slots = 0, o_segs = 0, o_adj_tiles = 0, o_adj_srcv = 0, o_rev_tiles = 0;
+    int64_t o_tiles = 0, o_slots = 0, o_segs = 0, o_bins = 0, o_adj_tiles = 0, o_adj_srcv = 0, o_rev_tiles = 0;
     std::vector<Tile> adj_tiles, rev_tiles;
     int64_t o_ck = 0, o_seg = 0, o_lam[2][3] = {{0, 0, 0}, {0, 0, 0}}, o_grad = 0, o_tab = 0,
             o_gsrc = 0, o_loss = 0, o_xref = 0, o_G = 0;
@@ -349,8 +351,9 @@ struct Plan {
     std::vector<Tile> tiles;
     int64_t ntiles[kTileClasses] = {0, 0, 0, 0}, tile_first[kTileClasses] = {0, 0, 0, 0};
     int64_t group_n[kTileClasses][kRoleGroups] = {};   // tiles of each role group, in group order within a class
-    std::vector<Group> slots;   // resident workgroups
-    int64_t nbins = 0;
+    std::vector<Group> slots;   // resident grids
+    std::vector<int32_t> bins;  // their places in the workgroups (empty: one each)
+    int64_t nbins = 0;          // resident workgroups
     std::vector<Group> segs;    // segments of the tiled executor
     bool spans[2] = {false, false};   // class 0, 1 holds spans
     int64_t nseg = 0, seg_nodes = 0;
@@ -549,8 +552,15 @@ bool groups_hold_cpml(const fdtd_plasma_desc *d, const std::vector<Group> &group
     return true;
 }
 
-// Resident workgroups, one a grid.  With skip_long, grids beyond kResMaxNodes
-// are left out (MIXED); otherwise such a grid makes it fail.
+// Resident grids and their workgroups.  With skip_long, grids beyond
+// kResMaxNodes are left out (MIXED); otherwise such a grid makes it fail.
+// A workgroup has the waves of the longest grid.  Up to kBinsAlone grids have
+// one each; more are dealt, the longest first, to the workgroup that holds
+// the fewest waves: a short grid alone in it would leave the other waves'
+// registers to nobody.  2048 steps FP64, a workgroup each against shared: one
+// grid of 1500 nodes and 2000 of 100-128 8.70 ms against 0.75; one of 4000 and
+// 1000 of 100-500 5.58, 1.29; 1000 of 100-4000 4.30, 3.55; 600 of 1000, which
+// fill their workgroups, 1.28, 1.25.
 bool build_bins(const fdtd_plasma_desc *d, Plan &p, bool skip_long = false)
 {
     int64_t longest = 1;
@@ -564,13 +574,35 @@ bool build_bins(const fdtd_plasma_desc *d, Plan &p, bool skip_long = false)
     p.resC = sh.C;
     p.resWaves = (int)group_waves(longest, sh.C);
     p.slots.clear();
-    p.nbins = 0;
-    int64_t o = 0;
+    p.bins.clear();
+    int64_t o = 0, waves = 0;
     for (int64_t b = 0; b < d->batch; o += d->cells[b], ++b) {
         const int64_t n = d->cells[b];
         if (n > kResMaxNodes) continue;
         push_group(d, p.slots, p.resC, b, o, 0, n, 0, n);
-        ++p.nbins;
+        waves += p.slots.back().nwaves;
+    }
+    const int64_t ngrids = (int64_t)p.slots.size(), B = p.resWaves;
+    p.nbins = ngrids;
+    if (ngrids <= kBinsAlone || B == 1) return true;
+    std::vector<int32_t> order(ngrids);
+    for (int64_t i = 0; i < ngrids; ++i) order[i] = (int32_t)i;
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int32_t a, int32_t b) { return p.slots[a].nwaves > p.slots[b].nwaves; });
+    p.nbins = std::max((waves + B - 1) / B, kBinsAlone);
+    std::set<std::pair<int64_t, int64_t>> load;           // (waves held, workgroup)
+    for (int64_t q = 0; q < p.nbins; ++q) load.insert({0, q});
+    p.bins.assign(p.nbins * B, -1);
+    for (int32_t i : order) {
+        const int64_t w = p.slots[i].nwaves;
+        if (load.begin()->first + w > B) {
+            load.insert({0, p.nbins++});
+            p.bins.resize(p.nbins * B, -1);
+        }
+        const auto [held, q] = *load.begin();
+        load.erase(load.begin());
+        for (int64_t k = 0; k < w; ++k) p.bins[q * B + held + k] = (i << kBinShift) | (int32_t)k;
+        load.insert({held + w, q});
     }
     return true;
 }
@@ -783,7 +815,11 @@ int plan(const fdtd_plasma_desc *d, Plan &p)
             for (int c = 0; c < 2; ++c) build_spans(d, p, c);
         }
     }
-    if (p.exec != FDTD_EXEC_RESIDENT && p.exec != FDTD_EXEC_MIXED) { p.slots.clear(); p.nbins = 0; }
+    if (p.exec != FDTD_EXEC_RESIDENT && p.exec != FDTD_EXEC_MIXED) {
+        p.slots.clear();
+        p.bins.clear();
+        p.nbins = 0;
+    }
 
     // sample window: up to 16384 steps, at most ~256 MiB of samples
     {
@@ -874,6 +910,7 @@ int plan(const fdtd_plasma_desc *d, Plan &p)
         L.total = tables;
         p.o_tiles = L.take((int64_t)sizeof(Tile) * std::max<size_t>(1, p.tiles.size()));
         p.o_slots = p.o_segs = L.take((int64_t)sizeof(Group) * std::max<size_t>(1, p.slots.size() + p.segs.size()));
+        if (!p.bins.empty()) p.o_bins = L.take(4 * (int64_t)p.bins.size());
     };
     take_tables();
     if (p.nseg && L.total > st && tables + plain <= st) {
@@ -1053,7 +1090,7 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
             const bool fork = h->side && (h->ntiles[2] || h->ntiles[3] || h->nseg) && !h->profiling;
             auto segments = [&](hipStream_t st) {
                 if (h->nseg)
-                    launch_group<T>(g, s, h->cur, h->cur ^ 1, h->d_segs, h->nseg, h->seg_waves, kSegC, (int)k, slot, st);
+                    launch_segments<T>(g, s, h->cur, h->d_segs, h->nseg, h->seg_waves, (int)k, slot, st);
             };
             auto on_side = [&](int c) { return fork && c >= 2; };
             if (fork) {
@@ -1090,8 +1127,7 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
             hipStream_t rs = fork ? h->side : h->stream;
             if (fork && (e = fork_side(h)) != hipSuccess) return lost_state(h, e);
             prof_begin(h, "resident", h->class_nodes[kTileClasses]);
-            launch_group<T>(g, s, h->cur, out, h->d_slots, h->nbins, h->resWaves, h->resC, (int)k, slot,
-                               rs);
+            launch_bins<T>(g, s, h->cur, out, h->d_slots, h->d_bins, h->nbins, h->resWaves, h->resC, (int)k, slot, rs);
             prof_end(h);
             int cur = h->cur;
             for (int64_t done = 0; done < k; done += h->Kh) {
@@ -1109,8 +1145,8 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
         } else {
             k = std::min<int64_t>(left, room);
             prof_begin(h, "resident", h->real_nodes);
-            launch_group<T>(g, s, h->cur, h->cur, h->d_slots, h->nbins, h->resWaves, h->resC, (int)k, slot,
-                               h->stream);
+            launch_bins<T>(g, s, h->cur, h->cur, h->d_slots, h->d_bins, h->nbins, h->resWaves, h->resC, (int)k, slot,
+                           h->stream);
             prof_end(h);
         }
         if (h->exec != FDTD_EXEC_RESIDENT) h->cur ^= 1;
@@ -1339,6 +1375,7 @@ int create_impl(const fdtd_plasma_desc *desc, Plan &p, void *dev_workspace, size
         h->n_rev_tiles = (int64_t)p.rev_tiles.size();
     }
     h->d_slots = (Group *)(w + p.o_slots);
+    h->d_bins = p.bins.empty() ? nullptr : (int32_t *)(w + p.o_bins);
     h->d_segs = (Group *)(w + p.o_segs);
     h->nseg = p.nseg;
     h->seg_waves = p.seg_waves;
@@ -1371,6 +1408,7 @@ int create_impl(const fdtd_plasma_desc *desc, Plan &p, void *dev_workspace, size
         e = H2D(h->d_tiles, p.tiles.data(), sizeof(Tile) * p.tiles.size());
     if (e == hipSuccess && !p.slots.empty())
         e = H2D(h->d_slots, p.slots.data(), sizeof(Group) * p.slots.size());
+    if (e == hipSuccess && !p.bins.empty()) e = H2D(h->d_bins, p.bins.data(), 4 * p.bins.size());
     if (e == hipSuccess && !p.segs.empty())
         e = H2D(h->d_segs, p.segs.data(), sizeof(Group) * p.segs.size());
     if (e == hipSuccess && !p.adj_tiles.empty())

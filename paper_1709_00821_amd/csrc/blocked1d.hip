@@ -396,19 +396,23 @@ template void launch_tiled<double>(const Grids &, State<double> &, int, const Ti
 // own, and is added to all; the lane of a probe writes its nodes' E to the
 // block's sample buffer and the others to a slot nobody reads.  Neither needs
 // a branch, an exec mask or a register picked at run time.
-template <int C, int WAVES>
+//
+// BINS: a workgroup holds several groups, dealt to its waves by a table (bins of
+// build_bins); then every wave has a source table of its own.
+template <int C, int WAVES, bool BINS>
 struct GroupLds {
     double edge[2][2][WAVES][3][kGroupHalo];    // [copy][left, right edge of the wave's own nodes][E, H, Q]
-    double src[2][64][C];                     // 64 steps' source values [owner, halo][step][register]
+    double src[BINS ? WAVES : 2][64][C];      // 64 steps' source values [wave; owner, halo][step][register]
     double zero[C];
     double probe[WAVES][2][kGroupHalo][C];      // the block's E of the lane holding each of two probes
     double sink[64][C];
 };
 
-template <typename T, int C, int WAVES, bool PLASMA, bool CPML, int ROLE>
-__device__ __forceinline__ void group_wave(const Grids &g, const State<T> &s, int cur, int out,
-                                              const Group &gr, const GroupWave &wv, GroupLds<C, WAVES> &lds, int w,
-                                              int lane, int nsteps, int slot0)
+// Wave w of the workgroup as wave gw of its group.
+template <typename T, int C, int WAVES, bool BINS, bool PLASMA, bool CPML, int ROLE>
+__device__ __forceinline__ void group_wave(const Grids &g, const State<T> &s, int cur, int out, const Group &gr,
+                                           const GroupWave &wv, GroupLds<C, WAVES, BINS> &lds, int w, int gw,
+                                           int lane, int nsteps, int slot0)
 {
     typedef Chunk<T, C, PLASMA, CPML> K;
     typedef typename K::R R;
@@ -447,7 +451,7 @@ __device__ __forceinline__ void group_wave(const Grids &g, const State<T> &s, in
         // the two waves that may hold the source: the one that owns its node,
         // and a neighbour in its halo
         const int64_t sn = g.src[b];
-        src_tab = &lds.src[role.src_lane >= 0 && sn >= wv.own_lo && sn < wv.own_hi ? 0 : 1][0][0];
+        src_tab = &lds.src[BINS ? w : role.src_lane >= 0 && sn >= wv.own_lo && sn < wv.own_hi ? 0 : 1][0][0];
         if (w == 0 && lane < C) lds.zero[lane] = 0.0;
         if (role.src_lane >= 0) {
 #pragma unroll
@@ -524,7 +528,7 @@ __device__ __forceinline__ void group_wave(const Grids &g, const State<T> &s, in
             const int c = (base / kGroupHalo) & 1;
             // Q crosses only between waves that both carry it: a vacuum
             // wave's nodes keep Q = 0 on both sides
-            const bool ql = PLASMA && has_l && ((gr.plasma >> (w - 1)) & 1), qr = PLASMA && ((gr.plasma >> (w + 1)) & 1);
+            const bool ql = PLASMA && has_l && ((gr.plasma >> (gw - 1)) & 1), qr = PLASMA && ((gr.plasma >> (gw + 1)) & 1);
 #pragma unroll
             for (int i = 0; i < C; ++i) {
                 const int l = (int)(k0 + i) - wv.own_lo, r = (int)(k0 + i) - (wv.own_hi - kGroupHalo);
@@ -587,28 +591,39 @@ __device__ __forceinline__ void group_wave(const Grids &g, const State<T> &s, in
     chunk_store<T, C, PLASMA, CPML>(ck, g, s, out, b, off, n, k0, st_lo, st_hi);
 }
 
-template <typename T, int C, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_group(Grids g, State<T> s, int cur, int out,
-                                                         const Group *groups, int nsteps, int slot0)
+template <typename T, int C, int WAVES, bool BINS>
+__global__ __launch_bounds__(WAVES * 64) void k_group(Grids g, State<T> s, int cur, int out, const Group *groups,
+                                                      const int32_t *bins, int nsteps, int slot0)
 {
-    __shared__ GroupLds<C, WAVES> lds;
+    __shared__ GroupLds<C, WAVES, BINS> lds;
     const int lane = threadIdx.x & 63;
     const int w = uniform(threadIdx.x >> 6);
-    const Group gr = groups[blockIdx.x];
+    int64_t at = blockIdx.x;
+    int gw = w;
+    bool idle = false;
+    if constexpr (BINS) {
+        if (bins) {
+            const int32_t e = bins[(int64_t)blockIdx.x * (blockDim.x >> 6) + w];
+            idle = e < 0;
+            at = idle ? 0 : e >> kBinShift;
+            gw = e & ((1 << kBinShift) - 1);
+        }
+    }
+    const Group gr = groups[at];
     // every path takes the same barriers: one after its loads, one a meeting
-    if (w >= gr.nwaves) {
+    if (idle || gw >= gr.nwaves) {
         __syncthreads();
         for (int base = kGroupHalo; base < nsteps; base += kGroupHalo) __syncthreads();
         return;
     }
-    const GroupWave wv = group_wave_at(gr, w, C);
-    const int role = (w < 10 ? gr.role[0] >> (3 * w) : gr.role[1] >> (3 * (w - 10))) & 7;
+    const GroupWave wv = group_wave_at(gr, gw, C);
+    const int role = (gw < 10 ? gr.role[0] >> (3 * gw) : gr.role[1] >> (3 * (gw - 10))) & 7;
 #define FDTDP_WAVE(PLASMA, CPML, ROLE) \
-    group_wave<T, C, WAVES, PLASMA, CPML, ROLE>(g, s, cur, out, gr, wv, lds, w, lane, nsteps, slot0)
+    group_wave<T, C, WAVES, BINS, PLASMA, CPML, ROLE>(g, s, cur, out, gr, wv, lds, w, gw, lane, nsteps, slot0)
     // layers at two nodes a lane only (kCpmlC; the register file)
     if constexpr (C == kCpmlC) {
-        if ((gr.cpml >> w) & 1) {
-            if ((gr.plasma >> w) & 1) {
+        if ((gr.cpml >> gw) & 1) {
+            if ((gr.plasma >> gw) & 1) {
                 FDTDP_WAVE(true, true, kResGeneral);
             } else {
                 switch (role) {
@@ -620,7 +635,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_group(Grids g, State<T> s, int c
             return;
         }
     }
-    if ((gr.plasma >> w) & 1) {
+    if ((gr.plasma >> gw) & 1) {
         switch (role) {
         case kResPlain: FDTDP_WAVE(true, false, kResPlain); break;
         case kResInner: FDTDP_WAVE(true, false, kResInner); break;
@@ -643,22 +658,33 @@ __global__ __launch_bounds__(WAVES * 64) void k_group(Grids g, State<T> s, int c
 }
 
 template <typename T>
-void launch_group(const Grids &g, State<T> &s, int cur, int out, const Group *groups, int64_t ngroups, int waves,
-                  int C, int nsteps, int slot0, hipStream_t st)
+void launch_bins(const Grids &g, State<T> &s, int cur, int out, const Group *groups, const int32_t *bins, int64_t nbins,
+                 int waves, int C, int nsteps, int slot0, hipStream_t st)
 {
-    const dim3 grid((unsigned)ngroups), blk((unsigned)(64 * waves));
+    const dim3 grid((unsigned)nbins), blk((unsigned)(64 * waves));
 #define FDTDP_GROUP(I)                                                                                            \
-    hipLaunchKernelGGL((k_group<T, kGroupShapes[I].C, kGroupShapes[I].waves>), grid, blk, 0, st, g, s, cur, out,  \
-                       groups, nsteps, slot0)
+    hipLaunchKernelGGL((k_group<T, kGroupShapes[I].C, kGroupShapes[I].waves, true>), grid, blk, 0, st, g, s, cur, \
+                       out, groups, bins, nsteps, slot0)
     if (C == kGroupShapes[0].C) FDTDP_GROUP(0);
     else if (C == kGroupShapes[1].C) FDTDP_GROUP(1);
     else FDTDP_GROUP(2);
 #undef FDTDP_GROUP
 }
 
-template void launch_group<float>(const Grids &, State<float> &, int, int, const Group *, int64_t, int, int,
-                                  int, int, hipStream_t);
-template void launch_group<double>(const Grids &, State<double> &, int, int, const Group *, int64_t, int, int,
-                                   int, int, hipStream_t);
+template <typename T>
+void launch_segments(const Grids &g, State<T> &s, int cur, const Group *segs, int64_t nseg, int waves, int nsteps,
+                     int slot0, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_group<T, kSegC, kSegWaves, false>), dim3((unsigned)nseg), dim3((unsigned)(64 * waves)), 0, st,
+                       g, s, cur, cur ^ 1, segs, (const int32_t *)nullptr, nsteps, slot0);
+}
+
+#define FDTDP_INST(T)                                                                                             \
+    template void launch_bins<T>(const Grids &, State<T> &, int, int, const Group *, const int32_t *, int64_t, int, \
+                                 int, int, int, hipStream_t);                                                     \
+    template void launch_segments<T>(const Grids &, State<T> &, int, const Group *, int64_t, int, int, int, hipStream_t);
+FDTDP_INST(float)
+FDTDP_INST(double)
+#undef FDTDP_INST
 
 }  // namespace fdtdp

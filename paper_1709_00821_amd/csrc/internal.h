@@ -124,6 +124,9 @@ struct GroupShape {
     constexpr int64_t nodes() const { return (int64_t)waves * (64 * C - 2 * kGroupHalo) + 2 * kGroupHalo; }
 };
 constexpr GroupShape kGroupShapes[3] = {{2, 16}, {4, 16}, {6, 12}};
+// Up to this many resident grids have a workgroup (and a CU) each; of more,
+// short ones share.
+constexpr int64_t kBinsAlone = 256;
 // The longest grid the resident executor takes.
 constexpr int64_t kResMaxNodes = 4096;
 static_assert(kGroupShapes[2].nodes() >= kResMaxNodes, "the widest shape holds the longest grid");
@@ -238,12 +241,18 @@ void launch_adj_tiled(const Grids &g, const AdjTileArgs<T> &a, const Tile *tiles
 constexpr int kAdjCells = 128, kAdjHalo = 48;
 constexpr int kAdjPrefetch = 6;   // steps of forward state the reverse sweep loads ahead
 
-// Workgroups of `waves` waves, C nodes a lane.  Reads buffer cur, writes buffer
-// out (cur itself for a whole-run resident call, the other buffer for segments
-// or when bins and tiles share a pass).
+// Workgroups of `waves` waves, C nodes a lane, a window's steps of whole grids:
+// a group each, or, with a table `bins` [workgroup][wave], several (group <<
+// kBinShift | wave of the group, -1: idle).  Reads buffer cur, writes buffer out
+// (cur itself, or the other one where bins and tiles share a pass).
+constexpr int kBinShift = 4;
 template <typename T>
-void launch_group(const Grids &g, State<T> &s, int cur, int out, const Group *groups, int64_t ngroups, int waves,
-                  int C, int nsteps, int slot0, hipStream_t st);
+void launch_bins(const Grids &g, State<T> &s, int cur, int out, const Group *groups, const int32_t *bins, int64_t nbins,
+                 int waves, int C, int nsteps, int slot0, hipStream_t st);
+// A pass of segments (kSegC nodes a lane) into the other buffer.
+template <typename T>
+void launch_segments(const Grids &g, State<T> &s, int cur, const Group *segs, int64_t nseg, int waves, int nsteps,
+                     int slot0, hipStream_t st);
 
 // Spans (tiles whose flags are their waves) of vacuum or plasma nodes, advanced
 // nsteps.  kSpanC: nodes a lane of either class.

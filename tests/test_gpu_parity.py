@@ -513,6 +513,34 @@ def test_group_of_one_wave_bitwise(G, ns, bc):
                     assert np.array_equal(F[b][k], Fs[b][k]), (ex, P, b, k)
 
 
+@pytest.mark.parametrize("bc", ["mur", "pec"])
+@pytest.mark.parametrize("longest", [200, 1568, 3000, 4096])
+def test_resident_grids_that_share_a_workgroup_bitwise(G, longest, bc):
+    """More grids than CUs, one of the longest length of each shape and the rest
+    from three nodes on, so that workgroups hold several (resident, and MIXED with
+    a tiled grid beside): every grid with the bits it has alone on the per-step
+    path, over two runs that are no whole number of meetings."""
+    rng = np.random.default_rng(longest)
+    ns = [longest] + [int(n) for n in rng.integers(6, 300, 300)] + [longest // 2 + 6]
+    probs = [W.random_slab(rng, n, bc=bc, n_freqs=3) for n in ns]
+    probs = [q.copy(freqs=probs[0].freqs) for q in probs]
+    T = 83
+    say(f"case shared workgroups longest={longest} {bc}")
+    Xs, Fs = gpu_run(G, probs, T, exec="step")
+    for ex, prs in (("resident", probs), ("mixed", probs + [W.random_slab(rng, 9000, bc=bc, n_freqs=3)
+                                                            .copy(freqs=probs[0].freqs)])):
+        with G.FdtdPlasma(prs, exec=ex) as h:
+            h.run(T)
+            X = h.spectra()
+            h.run(40).step(T - 40)
+            assert np.array_equal(X, h.spectra())
+            F = [h.fields(b) for b in range(len(probs))]
+        assert np.array_equal(X[:len(probs)], Xs), ex
+        for b in range(len(probs)):
+            for k in ("E", "H", "J"):
+                assert np.array_equal(F[b][k], Fs[b][k]), (ex, b, ns[b], k)
+
+
 @pytest.mark.parametrize("prec,K", [("f64", 64), ("f64", 52), ("f32", 60)])
 def test_spans_bitwise(G, prec, K):
     """Three long plasma grids whose tiles become spans of up to four waves, with

@@ -429,8 +429,14 @@ void sampled_steps(fdtd3d *h, int n)
 }
 
 // E and H rows of the incident grid at the n-th step from here
-const double *Ei_at(const fdtd3d *h, int64_t n) { return h->at<double>(h->pl.oEi) + (h->steps % kAuxBatch + n) * h->pl.na; }
-const double *Hi_at(const fdtd3d *h, int64_t n) { return h->at<double>(h->pl.oHi) + (h->steps % kAuxBatch + n + 1) * h->pl.na; }
+const double *Ei_at(const fdtd3d *h, int64_t n)
+{
+    return h->at<double>(h->pl.oEi) + (h->steps % kAuxBatch + n) * h->pl.na;
+}
+const double *Hi_at(const fdtd3d *h, int64_t n)
+{
+    return h->at<double>(h->pl.oHi) + (h->steps % kAuxBatch + n + 1) * h->pl.na;
+}
 
 template <typename T>
 void fused_step(fdtd3d *h)
@@ -448,15 +454,16 @@ void fused_step(fdtd3d *h)
     sampled_steps<T>(h, 1);
 }
 
-// One step of the two-kernel executor.  pend: the slot of the last step's E
-// samples, taken along by this step's H pass (-1: none).
+// One step of the two-kernel executor on the whole grid.  pend: the slot of
+// the last step's E samples, taken along by this step's H pass (-1: none; a
+// grid in slabs, whose points are listed by plane, samples after the step).
 template <typename T>
 int split_step(fdtd3d *h, int pend)
 {
     const Fields3<T> f = fields_of<T>(h, 0);
     const Cpml3<T> c = cpml_of<T>(h, 0, 0);
     const Samples3<T> none{};
-    const bool pts = h->pl.npts > 0 && h->pl.F > 0;
+    const bool pts = h->pl.npts > 0 && h->pl.F > 0 && !h->pl.slabp;
     ProfRec3 r;
     aux_batch(h);
     prof_begin(h, 0, (double)h->pl.N, r);
@@ -466,6 +473,7 @@ int split_step(fdtd3d *h, int pend)
     launch_e3d<T>(h->geo, pts ? samples3<T>(h, h->first[1], h->pl.npts, h->slot) : none, f, plasma_of<T>(h), c, Hi_at(h, 0),
                   source3(h, h->steps + 1), h->stream);
     prof_end(h, r);
+    if (h->pl.slabp && h->pl.npts > 0) sample_points<T>(h, f, samples3<T>(h, 0, h->pl.npts, h->slot));
     h->steps += 1;
     return pts ? h->slot : -1;
 }
@@ -500,21 +508,28 @@ void slab_steps(fdtd3d *h, int n)
     sampled_steps<T>(h, n);
 }
 
+// The steps of `left` that can go slab by slab now: within the sample window
+// and the incident grid's batch.
+int64_t slab_run(const fdtd3d *h, int64_t left)
+{
+    if (!h->pl.slabp) return 0;
+    int64_t n = std::min<int64_t>(std::min<int64_t>(kSlabSteps, left), kAuxBatch - h->steps % kAuxBatch);
+    if (h->pl.npts > 0 && h->pl.F > 0) n = std::min<int64_t>(n, h->pl.K - h->slot);
+    return n;
+}
+
 template <typename T>
 int advance(fdtd3d *h, int64_t nsteps)
 {
-    const bool pts = h->pl.npts > 0 && h->pl.F > 0;
     int pend = -1;
     for (int64_t s = 0; s < nsteps;) {
         int64_t n = 1;
         if (h->pl.exec == FDTD3D_EXEC_FUSED) {
             fused_step<T>(h);
-        } else if (h->pl.slabp) {
-            // within the sample window and the incident grid's batch
-            n = std::min<int64_t>(std::min<int64_t>(kSlabSteps, nsteps - s), kAuxBatch - h->steps % kAuxBatch);
-            if (pts) n = std::min<int64_t>(n, h->pl.K - h->slot);
+        } else if ((n = slab_run(h, nsteps - s)) >= kSlabLeast) {
             slab_steps<T>(h, (int)n);
         } else {
+            n = 1;
             pend = split_step<T>(h, pend);
             if (pend >= 0 && (s + 1 == nsteps || pend + 1 == h->pl.K)) {
                 sample_points<T>(h, fields_of<T>(h, 0), samples3<T>(h, 0, h->first[1], pend));
@@ -734,7 +749,8 @@ int fdtd3d_run(fdtd3d *h, int64_t nsteps)
     if (nsteps < 0) return fail3(FDTD_E_INVALID, "nsteps %lld < 0", (long long)nsteps);
     // (slabs take many launches a step, each long enough to hide the next one's)
     const int64_t slabs = h->pl.slabp ? (h->d.nx + h->pl.slabp - 1) / h->pl.slabp : 0;
-    const bool eager = slabs > 0 && 2 * slabs * nsteps > kGraphNodes;
+    const int64_t launches = h->pl.npts > 0 && h->pl.F > 0 ? 3 : 2;   // H, E, samples
+    const bool eager = slabs > 0 && launches * slabs * nsteps > kGraphNodes;
     if (h->stream == nullptr || h->prof || eager) {
         if (eager && h->stream) {
             hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;

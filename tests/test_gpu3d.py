@@ -269,6 +269,29 @@ def test_3d_slabs_bitwise(G, prec, nx, slots):
     assert all(np.array_equal(a, b) for a, b in zip(got["fused"], got["split"]))
 
 
+@pytest.mark.parametrize("slots", [1, 3, 32])
+def test_3d_few_steps_of_a_grid_in_slabs_bitwise(G, slots):
+    """Calls and sample windows of fewer steps than pay for slabs, which go over
+    the whole grid, mixed with longer ones, against the one-pass executor."""
+    nx, ny, nz = 33, 560, 520
+    p = W.sphere_c3(60, cpml=3, n_freqs=2, box_dft=False)
+    wp2 = np.zeros((3, nx, ny, nz))
+    wp2[:, 6:20, 12:200, 14:150] = p.wp2.max()
+    pts = np.array([(c, i, 20 + 3 * i, 30 + c) for i in range(nx) for c in range(6)], np.int32)
+    p = p.copy(nx=nx, ny=ny, nz=nz, wp2=wp2, nu=np.full((nx, ny, nz), 1e10), b0=6, b1=25,
+               points=pts[np.random.default_rng(slots).permutation(len(pts))])
+    got = {}
+    for ex in ("fused", "split"):
+        say(f"case 3d few steps {nx}x{ny}x{nz} slots={slots} {ex}")
+        with G.FdtdPlasma3D(p, precision="f32", sample_slots=slots, exec=ex) as h:
+            h.run(4)
+            for n in (1, 2, 1, 17, 1, 3, 1, 1, 13):
+                h.step(n)
+            got[ex] = [h.field(nm) for nm in ("Ex", "Hy", "Jx")] + [h.spectra()]
+    assert np.any(got["split"][2])
+    assert all(np.array_equal(a, b) for a, b in zip(got["fused"], got["split"]))
+
+
 @pytest.mark.parametrize("nx,x_planes", [(25, 1), (27, 5), (30, 1), (30, 13)])
 def test_3d_slabs_of_few_planes_bitwise(G, nx, x_planes):
     """The shortest grids that are stepped in slabs, with the planes a thread

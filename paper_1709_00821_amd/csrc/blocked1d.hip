@@ -379,8 +379,9 @@ template void launch_tiled<double>(const Grids &, State<double> &, int, const Ti
 
 // ------------------------------------------------------------- resident
 
-// One workgroup a group (a whole grid, or a segment of one).  Each wave owns a run of nodes and holds kGroupHalo more on each side
-// that another wave owns; it recomputes those, so waves meet only every
+// One workgroup a group (a whole grid, or a segment of one).  Each wave owns a
+// run of nodes and holds kGroupHalo more on each side that another wave owns;
+// it recomputes those, so waves meet only every
 // kGroupHalo steps, when the owners' values of E, H and Q replace the
 // halo's through LDS (psi never: a CPML layer lies in
 // its wave's own nodes), one barrier a meeting (two copies of the buffer: a wave

@@ -65,17 +65,14 @@ __device__ __forceinline__ int slab(int64_t n, int64_t len, int P)
     return -1;
 }
 
-// The CPML terms of one cell's H (or E) update, read before any arithmetic so
-// that no layer's loads wait on another's, or on the fields' (with each axis
-// reading its own as it came to them, a cell in a layer waited on up to three
-// more rounds of loads: the 96^3 FP64 sphere 68 -> 64 us a step).  i and j are
-// the same for the whole wave, so the x and y layers are scalar branches.
-template <typename T>
+// Where one cell lies in the CPML layers.  i and j are the same for the whole
+// wave, so the x and y layers are scalar branches.  Every axis reads its
+// auxiliaries when the update comes to it: read together before any arithmetic they
+// take 24 more registers in FP64 (H pass 6 -> 4 waves a SIMD, E pass 4 -> 3; 200^3 181 +
+// 302 -> 192 + 323 us a step).
 struct Layers {
-    bool in[3];
-    int64_t base[3];              // of the wave, in elements
-    uint32_t off[3];              // of the lane, in bytes
-    T b[3], a[3], psi[3][2];
+    int s[3];                     // place in the layer, -1 outside it
+    int64_t at[3];                // element of its auxiliary arrays
 };
 
 // An element of a wave's row: the same start for all lanes, a byte offset each
@@ -87,43 +84,32 @@ __device__ __forceinline__ T &elem(T *f, int64_t base, uint32_t off)
     return *(T *)((C *)(f + base) + off);
 }
 
-// (the wave's nodes are k0 + lane)
-template <typename T>
-__device__ __forceinline__ Layers<T> layers_load(const Geo3 &g, const T *const (&pin)[3][2], const T *tab, int row,
-                                                 int64_t i, int64_t j, int64_t k0, uint32_t lane)
+__device__ __forceinline__ Layers layers_of(const Geo3 &g, int64_t i, int64_t j, int64_t k)
 {
-    Layers<T> q;
+    Layers q;
     const int P = g.P, P2 = 2 * g.P;
-    const int s[3] = {P > 0 && !g.px ? slab(i, g.nx, P) : -1, P > 0 && !g.py ? slab(j, g.ny, P) : -1,
-                      P > 0 ? slab(k0 + lane, g.nz, P) : -1};
-    q.base[0] = ((int64_t)s[0] * g.ny + j) * g.nz + k0;
-    q.base[1] = (i * P2 + s[1]) * g.nz + k0;
-    q.base[2] = (i * g.ny + j) * P2;
-    q.off[0] = q.off[1] = lane * (uint32_t)sizeof(T);
-    q.off[2] = (uint32_t)s[2] * (uint32_t)sizeof(T);
-#pragma unroll
-    for (int x = 0; x < 3; ++x) {
-        q.in[x] = s[x] >= 0;
-        if (q.in[x]) {
-            q.b[x] = tab[(x * 4 + row) * P2 + s[x]];
-            q.a[x] = tab[(x * 4 + row + 1) * P2 + s[x]];
-            q.psi[x][0] = elem(pin[x][0], q.base[x], q.off[x]);
-            q.psi[x][1] = elem(pin[x][1], q.base[x], q.off[x]);
-        }
-    }
+    q.s[0] = P > 0 && !g.px ? slab(i, g.nx, P) : -1;
+    q.s[1] = P > 0 && !g.py ? slab(j, g.ny, P) : -1;
+    q.s[2] = P > 0 ? slab(k, g.nz, P) : -1;
+    q.at[0] = ((int64_t)q.s[0] * g.ny + j) * g.nz + k;
+    q.at[1] = (i * P2 + q.s[1]) * g.nz + k;
+    q.at[2] = (i * g.ny + j) * P2 + q.s[2];
     return q;
 }
 
 // psi' = b psi + a dF for both derivatives across axis x (separately rounded,
-// as written), stored only by the cell's owner; each dF gains its psi'.
+// as written; row: of b in the table), stored only by the cell's owner; each dF
+// gains its psi'.
 template <typename T>
-__device__ __forceinline__ void layers_add(const Layers<T> &q, T *const (&pout)[3][2], int x, T &d0, T &d1, bool store)
+__device__ __forceinline__ void layers_add(const Layers &q, int x, const T *tab, int P, int row, const T *const (&pin)[3][2],
+                                           T *const (&pout)[3][2], T &d0, T &d1, bool store)
 {
-    if (!q.in[x]) return;
-    const T v0 = q.b[x] * q.psi[x][0] + q.a[x] * d0, v1 = q.b[x] * q.psi[x][1] + q.a[x] * d1;
+    if (q.s[x] < 0) return;
+    const T b = tab[(x * 4 + row) * 2 * P + q.s[x]], a = tab[(x * 4 + row + 1) * 2 * P + q.s[x]];
+    const T v0 = b * pin[x][0][q.at[x]] + a * d0, v1 = b * pin[x][1][q.at[x]] + a * d1;
     if (store) {
-        elem(pout[x][0], q.base[x], q.off[x]) = v0;
-        elem(pout[x][1], q.base[x], q.off[x]) = v1;
+        pout[x][0][q.at[x]] = v0;
+        pout[x][1][q.at[x]] = v1;
     }
     d0 = d0 + v0;
     d1 = d1 + v1;
@@ -133,12 +119,11 @@ __device__ __forceinline__ void layers_add(const Layers<T> &q, T *const (&pout)[
 
 // H^{n+1/2} of cell (i, j, k) from its E^n and the E^n of its +1 neighbours
 // (zero beyond a wall); hx, hy, hz hold H^{n-1/2} on entry.  CPML auxiliaries
-// (q, read by the caller) and the TF/SF correction (Einc^n) included.  Shared
-// by both executors.
+// and the TF/SF correction (Einc^n) included.  Shared by both executors.
 template <typename T>
-__device__ __forceinline__ void h_cell(const Geo3 &g, const Cpml3<T> &c, const Layers<T> &q, const double *Einc,
-                                       int64_t i, int64_t j, int64_t k, T ex, T ey, T ez, T ex_j, T ex_k, T ey_i,
-                                       T ey_k, T ez_i, T ez_j, T &hx, T &hy, T &hz, bool store)
+__device__ __forceinline__ void h_cell(const Geo3 &g, const Cpml3<T> &c, const double *Einc, int64_t i, int64_t j,
+                                       int64_t k, T ex, T ey, T ez, T ex_j, T ex_k, T ey_i, T ey_k, T ez_i, T ez_j,
+                                       T &hx, T &hy, T &hz, bool store)
 {
     T dEz_y = ez_j - ez;
     T dEy_z = ey_k - ey;
@@ -146,9 +131,10 @@ __device__ __forceinline__ void h_cell(const Geo3 &g, const Cpml3<T> &c, const L
     T dEz_x = ez_i - ez;
     T dEy_x = ey_i - ey;
     T dEx_y = ex_j - ex;
-    layers_add(q, c.outH, 0, dEz_x, dEy_x, store);
-    layers_add(q, c.outH, 1, dEz_y, dEx_y, store);
-    layers_add(q, c.outH, 2, dEy_z, dEx_z, store);
+    const Layers q = layers_of(g, i, j, k);
+    layers_add(q, 0, c.tab, g.P, 2, c.inH, c.outH, dEz_x, dEy_x, store);
+    layers_add(q, 1, c.tab, g.P, 2, c.inH, c.outH, dEz_y, dEx_y, store);
+    layers_add(q, 2, c.tab, g.P, 2, c.inH, c.outH, dEy_z, dEx_z, store);
     const T ch = (T)g.chd;
     hx = fmat(-ch, dEz_y - dEy_z, hx);
     hy = fmat(-ch, dEx_z - dEz_x, hy);
@@ -217,20 +203,24 @@ constexpr bool kLateJ = sizeof(T) == 8;
 template <typename T>
 struct PNode {
     bool on;
-    int64_t base;                 // compact index: of the wave's node k0, in elements,
-    uint32_t off;                 // and of the lane past it, in bytes
+    int64_t base;                 // compact index: of the wave's node k0 (or the lane's own), in elements,
+    uint32_t off;                 // and of the lane past it, in bytes (or none)
     T J[3];
     NodeCoef<T> cf[3];
 };
 
-template <typename T>
+// ROW: scalar row starts and a lane offset (elem), else one index a lane.  The E
+// pass takes the first in its plain way in FP64 (160^3 all plasma 220 us against 226)
+// and the second elsewhere (200^3 FP32 sphere 161 against 166-193, by the registers; the
+// one-pass kernel 136 VGPRs against 219 with the layers' too, 160^3 FP32 220 us a step against 300).
+template <bool ROW, typename T>
 __device__ __forceinline__ PNode<T> pnode_load(const Plasma3<T> &pl, int2 sp, int64_t off, int64_t k0, uint32_t lane)
 {
     PNode<T> n;
     const int64_t k = k0 + lane;
     n.on = k >= sp.x && k < sp.y;
-    n.base = off + (k0 - sp.x);
-    n.off = lane * (uint32_t)sizeof(T);
+    n.base = off + ((ROW ? k0 : k) - sp.x);
+    n.off = ROW ? lane * (uint32_t)sizeof(T) : 0;
     if (n.on) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -305,8 +295,8 @@ __device__ __forceinline__ T e_plasma_comp(const Geo3 &g, const Plasma3<T> &pl, 
 // caller), J^{n+1} (written in place).  Shared by both executors.
 template <typename T>
 __device__ __forceinline__ void e_cell(const Geo3 &g, const Plasma3<T> &pl, const PNode<T> &pn,
-                                       const Cpml3<T> &c, const Layers<T> &q, const double *Hinc, double sval,
-                                       int64_t i, int64_t j, int64_t k, T hx, T hy, T hz, T hx_j, T hx_k, T hy_i, T hy_k, T hz_i, T hz_j,
+                                       const Cpml3<T> &c, const double *Hinc, double sval, int64_t i, int64_t j,
+                                       int64_t k, T hx, T hy, T hz, T hx_j, T hx_k, T hy_i, T hy_k, T hz_i, T hz_j,
                                        T &e0, T &e1, T &e2)
 {
     T dHz_y = hz - hz_j;
@@ -315,9 +305,10 @@ __device__ __forceinline__ void e_cell(const Geo3 &g, const Plasma3<T> &pl, cons
     T dHz_x = hz - hz_i;
     T dHy_x = hy - hy_i;
     T dHx_y = hx - hx_j;
-    layers_add(q, c.outE, 0, dHz_x, dHy_x, true);
-    layers_add(q, c.outE, 1, dHz_y, dHx_y, true);
-    layers_add(q, c.outE, 2, dHy_z, dHx_z, true);
+    const Layers q = layers_of(g, i, j, k);
+    layers_add(q, 0, c.tab, g.P, 0, c.inE, c.outE, dHz_x, dHy_x, true);
+    layers_add(q, 1, c.tab, g.P, 0, c.inE, c.outE, dHz_y, dHx_y, true);
+    layers_add(q, 2, c.tab, g.P, 0, c.inE, c.outE, dHy_z, dHx_z, true);
     const T curl0 = dHz_y - dHy_z, curl1 = dHx_z - dHz_x, curl2 = dHy_x - dHx_y;
     if (!pn.on) {
         const T ce = (T)g.ced;
@@ -519,9 +510,8 @@ __global__ __launch_bounds__(256) void k_h3d(ArgsH3<T> arg)
             Const<ArgsH3<T>> *s = kernel_args<ArgsH3<T>>();
             const Geo3 gs = geo_arg(&s->g);
             const Cpml3<T> c = cpml_arg<T>(&s->c);
-            const Layers<T> lay = layers_load<T>(gs, c.inH, c.tab, 2, i, j, q.k0, lane);
-            h_cell<T>(gs, c, lay, global_ptr(s->Einc), i, j, q.k, e[0], e[1], e[2], ex_j, ex_k, ey_i, ey_k, ez_i, ez_j,
-                      v.h[0], v.h[1], v.h[2], true);
+            h_cell<T>(gs, c, global_ptr(s->Einc), i, j, q.k, e[0], e[1], e[2], ex_j, ex_k, ey_i, ey_k, ez_i, ez_j, v.h[0],
+                      v.h[1], v.h[2], true);
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -607,17 +597,16 @@ __global__ __launch_bounds__(256) void k_e3d(ArgsE3<T> arg)
             const Geo3 gs = geo_arg(&s->g);
             const Cpml3<T> c = cpml_arg<T>(&s->c);
             const Plasma3<T> pl = plasma_arg<T>(&s->pl);
-            const PNode<T> pn = pnode_load(pl, make_int2(v.lo, v.hi), v.off, q.k0, lane);
-            const Layers<T> lay = layers_load<T>(gs, c.inE, c.tab, 0, i, j, q.k0, lane);
-            e_cell<T>(gs, pl, pn, c, lay, global_ptr(s->Hinc), s->sval, i, j, q.k, v.h[0], v.h[1], v.h[2], hx_j, hx_k,
-                      hy_i, hy_k, hz_i, hz_j, v.e[0], v.e[1], v.e[2]);
+            const PNode<T> pn = pnode_load<false>(pl, make_int2(v.lo, v.hi), v.off, q.k0, lane);
+            e_cell<T>(gs, pl, pn, c, global_ptr(s->Hinc), s->sval, i, j, q.k, v.h[0], v.h[1], v.h[2], hx_j, hx_k, hy_i,
+                      hy_k, hz_i, hz_j, v.e[0], v.e[1], v.e[2]);
         } else {
             const T dHz_y = v.h[2] - hz_j, dHy_z = v.h[1] - hy_k, dHx_z = v.h[0] - hx_k;
             const T dHz_x = v.h[2] - hz_i, dHy_x = v.h[1] - hy_i, dHx_y = v.h[0] - hx_j;
             const T curl[3] = {dHz_y - dHy_z, dHx_z - dHz_x, dHy_x - dHx_y};
             if (plasma) {
                 const Plasma3<T> pl = plasma_arg<T>(&kernel_args<ArgsE3<T>>()->pl);
-                const PNode<T> pn = pnode_load(pl, make_int2(v.lo, v.hi), v.off, q.k0, lane);
+                const PNode<T> pn = pnode_load<sizeof(T) == 8>(pl, make_int2(v.lo, v.hi), v.off, q.k0, lane);
                 if (pn.on) {
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
@@ -631,8 +620,8 @@ __global__ __launch_bounds__(256) void k_e3d(ArgsE3<T> arg)
 #pragma unroll
                     for (int c = 0; c < 3; ++c) v.e[c] = fmat(ce, curl[c], v.e[c]);
                 }
-                } else {
-    #pragma unroll
+            } else {
+#pragma unroll
                 for (int c = 0; c < 3; ++c) v.e[c] = fmat(ce, curl[c], v.e[c]);
             }
         }
@@ -763,7 +752,7 @@ __global__ __launch_bounds__(256) void k_fused3d(Geo3 g, Fields3<T> fin, Fields3
         int2 spn = sp;
         int64_t ofn = of;
         if (!lead) {
-            pn = pnode_load(pl, sp, of, (int64_t)(kq * 63 - 1), (uint32_t)lane);
+            pn = pnode_load<false>(pl, sp, of, kq * 63 - 1, (uint32_t)lane);
             if (i + 1 < i1) {
                 spn.x = spans[(i + 1) * g.ny + j].x;
                 spn.y = spans[(i + 1) * g.ny + j].y;
@@ -773,17 +762,17 @@ __global__ __launch_bounds__(256) void k_fused3d(Geo3 g, Fields3<T> fin, Fields3
         if (i + 1 < i1) load(i + 1, nxt);
         T hx = cur.h[0], hy = cur.h[1], hz = cur.h[2];
         if (vk)
-            h_cell<T>(g, c, layers_load<T>(g, c.inH, c.tab, 2, gi, j, (int64_t)(kq * 63 - 1), (uint32_t)lane), Einc, gi, j, k, cur.e[0], cur.e[1], cur.e[2], cur.exj, cur.exk, cur.eyi, cur.eyk,
-                      cur.ezi, cur.ezj, hx, hy, hz, own && !lead);
+            h_cell<T>(g, c, Einc, gi, j, k, cur.e[0], cur.e[1], cur.e[2], cur.exj, cur.exk, cur.eyi, cur.eyk, cur.ezi,
+                      cur.ezj, hx, hy, hz, own && !lead);
         const T hxk = lane_up1(hx), hyk = lane_up1(hy);   // H at k-1
         if (own && !lead) {
             T mx = cur.hmx, my = zero, mz = cur.hmz;
             if (hasjm)
-                h_cell<T>(g, c, layers_load<T>(g, c.inH, c.tab, 2, gi, jm, (int64_t)(kq * 63 - 1), (uint32_t)lane), Einc, gi, jm, k, cur.m[0], cur.m[1], cur.m[2], cur.e[0], zero, cur.myi, cur.myk,
-                          zero, cur.e[2], mx, my, mz, false);
+                h_cell<T>(g, c, Einc, gi, jm, k, cur.m[0], cur.m[1], cur.m[2], cur.e[0], zero, cur.myi, cur.myk, zero,
+                          cur.e[2], mx, my, mz, false);
             T e0 = cur.e[0], e1 = cur.e[1], e2 = cur.e[2];
             const bool kin = k > 0;
-            e_cell<T>(g, pl, pn, c, layers_load<T>(g, c.inE, c.tab, 0, gi, j, (int64_t)(kq * 63 - 1), (uint32_t)lane), Hinc, sval, gi, j, k, hx, hy, hz, hasjm ? mx : zero, kin ? hxk : zero, hy_i,
+            e_cell<T>(g, pl, pn, c, Hinc, sval, gi, j, k, hx, hy, hz, hasjm ? mx : zero, kin ? hxk : zero, hy_i,
                       kin ? hyk : zero, hz_i, hasjm ? mz : zero, e0, e1, e2);
             const int64_t p = (gi * g.ny + j) * g.nz + k;
             fout.H[0][p] = hx;

@@ -1111,7 +1111,7 @@ int advance_t(fdtd_plasma *h, int64_t nsteps)
                     prof_end(h);
                 }
             if (h->nseg && !fork) {
-                prof_begin(h, kTiledNames[3], h->seg_nodes);
+                prof_begin(h, "segments", h->seg_nodes);
                 segments(h->stream);
                 prof_end(h);
             }

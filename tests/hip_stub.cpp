@@ -19,6 +19,8 @@ std::map<void *, Captured> graphs, execs;
 bool capturing = false;
 Captured capture;
 std::set<void *> recorded;         // events recorded in the capture in progress
+std::map<const void *, std::string> names;   // kernels by their host stubs
+std::map<std::string, long> launched;
 std::string fails;                 // the next call of this name fails
 int misuses = 0;
 long limit = 0;                    // the most bytes of one allocation (0: any)
@@ -55,6 +57,15 @@ int stub_misuses() { return misuses; }
 int stub_live() { return (int)(streams.size() + events.size() + graphs.size() + execs.size()); }
 long stub_waits() { return waits; }
 long stub_launches() { return launches; }
+// launches of the kernels whose (mangled) names hold `part`, since the last call
+long stub_launched(const char *part)
+{
+    long n = 0;
+    for (auto &l : launched)
+        if (l.first.find(part) != std::string::npos) n += l.second;
+    return n;
+}
+void stub_forget() { launched.clear(); }
 long stub_bad_grids() { return bad_grids; }
 
 hipError_t hipMalloc(void **p, size_t n)
@@ -122,13 +133,20 @@ hipError_t hipGraphInstantiate(hipGraphExec_t *e, hipGraph_t g, hipGraphNode_t *
 }
 hipError_t hipGraphExecDestroy(hipGraphExec_t e) { execs.erase(e); free(e); return hipSuccess; }
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return failing("hipGraphLaunch") ? hipErrorUnknown : hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *)
+{
+    static char *static_ws = (char *)aligned_alloc(256, 16 << 20);
+    *p = static_ws;
+    return hipSuccess;
+}
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return failing("hipGetLastError") ? hipErrorUnknown : hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "stand-in"; }
-hipError_t hipLaunchKernel(const void *, dim3 g, dim3 b, void **, size_t, hipStream_t)
+hipError_t hipLaunchKernel(const void *host, dim3 g, dim3 b, void **, size_t, hipStream_t)
 {
     ++launches;
+    ++launched[names[host]];
     if (g.x == 0 || g.y == 0 || g.z == 0 || (unsigned long)g.x * b.x > 0xFFFFFFFFul) ++bad_grids;
     return hipSuccess;
 }
@@ -143,7 +161,10 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *n, hipStream_t *s
     return hipSuccess;
 }
 void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
-void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
+void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *, void *, void *, void *, int *)
+{
+    names[host] = name;
+}
 void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 void __hipUnregisterFatBinary(void **) {}
 }

@@ -513,6 +513,25 @@ def test_group_of_one_wave_bitwise(G, ns, bc):
                     assert np.array_equal(F[b][k], Fs[b][k]), (ex, P, b, k)
 
 
+@pytest.mark.parametrize("n,cpml", [(300, 6), (801, 40), (1500, 60), (2900, 10)])
+@pytest.mark.parametrize("K", [20, 64])
+def test_fp32_segments_with_layers_bitwise(G, n, cpml, K):
+    """FP32 storage, whose bits depend on where launches end: segments that hold
+    the layers against tiles of two waves, which stay tiles, with the same steps a
+    launch."""
+    rng = np.random.default_rng(n + K)
+    p = W.random_slab(rng, n, bc="cpml", cpml_cells=cpml)
+    say(f"case fp32 segments with layers n={n} cpml={cpml} K={K}")
+    T = 205
+    with G.FdtdPlasma(p, precision="f32", exec="tiled", steps_per_pass=K) as h:
+        assert "segments" in h.profile(K), "no segments"
+    Xs, Fs = gpu_run(G, p, T, "f32", "tiled", steps_per_pass=K)
+    Xt, Ft = gpu_run(G, p, T, "f32", "tiled", steps_per_pass=K, tile_waves=2)
+    assert np.array_equal(Xs, Xt)
+    for k in ("E", "H", "J"):
+        assert np.array_equal(Fs[0][k], Ft[0][k]), k
+
+
 @pytest.mark.parametrize("bc", ["mur", "pec"])
 @pytest.mark.parametrize("longest", [200, 1568, 3000, 4096])
 def test_resident_grids_that_share_a_workgroup_bitwise(G, longest, bc):

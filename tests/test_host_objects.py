@@ -123,6 +123,84 @@ assert stub.stub_misuses() == 0 and stub.stub_bad_grids() == 0
 """
 
 
+KERNELS = CHILD + r"""
+stub.stub_launched.restype = ctypes.c_long
+def taken(p, prec="f64", exec="tiled", steps=64, **kw):
+    d, keep = make_desc(p, prec, exec, stream_handle=STREAM, **kw)
+    h = ctypes.c_void_p()
+    L.check(lib.fdtd_plasma_create(ctypes.byref(d), None, 0, ctypes.byref(h)))
+    stub.stub_forget()
+    assert lib.fdtd_plasma_step(h, steps) == 0
+    lib.fdtd_plasma_destroy(h)
+    return {k: stub.stub_launched(k.encode()) for k in ("k_spanI", "k_groupI", "k_tiledI", "k_step")}
+
+def long_grids(ns, plasma):
+    out = []
+    for n in ns:
+        p = W.large_c2(n=n, n_freqs=3, cpml=8)
+        wp2 = np.full(n, p.wp2.max() / 40) if plasma else np.zeros(n)
+        wp2[:100] = wp2[-100:] = 0.0
+        out.append(p.copy(wp2=wp2, src_cell=n // 2, probes=np.array([n // 2 - 700, n // 2 + 900])))
+    return out
+
+# the grids of the span tests become spans beside segments, with 256-node tiles they stay tiles
+plasma, vacuum = long_grids((1500007, 1511111, 1489999), True), long_grids((1900001, 1850011, 1799999), False)
+for prec, K in (("f64", 64), ("f32", 60)):
+    t = taken(plasma, prec, steps=K, tile_cells=512, steps_per_pass=K)
+    assert t["k_spanI"] == 1 and t["k_groupI"] == 1, t
+    t = taken(vacuum, prec, steps=K, tile_cells=512, vacuum_tile_cells=1024, steps_per_pass=K)
+    assert t["k_spanI"] >= 1 and t["k_groupI"] == 1, t
+    t = taken(plasma, prec, steps=K, tile_cells=256, steps_per_pass=K)
+    assert t["k_spanI"] == 0 and t["k_tiledI"] >= 1, t
+# the grids of the group tests: segments alone, or resident; with layers too thick for a segment, tiles
+for n in (245, 801, 1569, 2900):
+    p = W.random_slab(np.random.default_rng(n), n)
+    for ex in ("auto", "tiled", "resident"):
+        t = taken(p, exec=ex, steps=48)
+        assert t["k_groupI"] == 1 and t["k_tiledI"] == 0, (n, ex, t)
+p = W.random_slab(np.random.default_rng(1), 2900, bc="cpml", cpml_cells=120)
+t = taken(p)
+assert t["k_groupI"] == 0 and t["k_tiledI"] > 0, t
+assert taken(p.copy(cpml_cells=6), "f32", steps=48)["k_groupI"] == 1
+# a batch whose role tiles fill the GPU keeps them
+few, many = ([W.slab_c1(n=2000, slab=(800, 1100), src=200, probes=(100, 1800), n_freqs=2)] * k for k in (300, 900))
+assert taken(few, steps=48)["k_groupI"] == 1 and taken(many)["k_groupI"] == 0
+"""
+
+STATIC = CHILD + r"""
+stub.stub_launched.restype = ctypes.c_long
+MB16 = 16 << 20
+def plan(ns, fill):                       # fill: the unused table of layers, 32 B a node, to come near the limit
+    ps = [W.slab_c1(n=n, slab=(n // 3, n // 2), src=8, probes=(4,), n_freqs=2).copy(cpml_cells=fill) for n in ns]
+    d, keep = make_desc(ps, "f64", "tiled", stream_handle=STREAM)
+    b = ctypes.c_size_t()
+    L.check(lib.fdtd_plasma_workspace_bytes(ctypes.byref(d), ctypes.byref(b)))
+    return d, keep, b.value
+def kernels(d):
+    h = ctypes.c_void_p()
+    rc = lib.fdtd_plasma_create_static(ctypes.byref(d), ctypes.byref(h))
+    if rc: return rc
+    stub.stub_forget()
+    assert lib.fdtd_plasma_step(h, 40) == 0
+    lib.fdtd_plasma_destroy(h)
+    return stub.stub_launched(b"k_groupI"), stub.stub_launched(b"k_tiledI")
+# 90 short grids: their segments' table is 90 x 8 bytes longer than the tiles'
+ns = [380] * 90
+while plan(ns, 1)[2] > MB16 - 200000: ns = [n - 8 for n in ns]
+d, keep, b = plan(ns, 1)
+assert kernels(d) == (1, 0), (kernels(d), b, ns[0])               # room to spare: segments
+fill = 1
+for _ in range(2):                        # (the transform's wider scratch space goes first)
+    fill += (MB16 - plan(ns, fill)[2]) // 32 + 128
+    while plan(ns, fill)[2] > MB16: fill -= 8
+d, keep, b = plan(ns, fill)
+assert MB16 - 256 < b <= MB16, (b, MB16 - b, fill)
+assert kernels(d)[1] > 0 and kernels(d)[0] == 0, (kernels(d), b)     # the tiles' table still fits, the segments' does not: tiles
+d, keep, b = plan(ns, fill + 8)
+assert b > MB16 and kernels(d) == L.E_WORKSPACE
+"""
+
+
 @pytest.fixture(scope="module")
 def stub(tmp_path_factory):
     so = tmp_path_factory.mktemp("stub") / "hip_stub.so"
@@ -153,6 +231,18 @@ def test_a_run_that_was_not_captured_leaves_the_state(stub, what):
 @pytest.mark.parametrize("what", ["hipEventRecord", "hipStreamWaitEvent"])
 def test_a_step_whose_streams_did_not_wait_is_reported(stub, what):
     child(EVENTS, stub, what)
+
+
+def test_the_kernels_a_problem_takes(stub):
+    """The bit-for-bit tests of spans and segments compare them with tiles only
+    if the problems take them."""
+    child(KERNELS, stub)
+
+
+def test_the_static_workspace_at_its_limit(stub):
+    """Where the table of segments would push a problem past the static
+    workspace and that of the plain tiles does not, it runs as tiles."""
+    child(STATIC, stub)
 
 
 def test_2d_takes_a_workspace_of_one_copy_of_the_fields(stub):

@@ -140,7 +140,8 @@ constexpr int kCpmlC = kGroupShapes[0].C;
 // then spread over the SIMDs, not all on the first (700 grids of 20 to 128
 // nodes, 4096 steps FP32: 4.6 -> 1.5 ms with the step above).
 constexpr int kSegC = 2, kSegWaves = 8;
-static_assert(kSegC == kCpmlC, "segments hold layers");
+static_assert(kSegC == kCpmlC && kSegC == kGroupShapes[0].C && kSegWaves <= kGroupShapes[0].waves,
+              "segments hold layers, and run as groups of the first shape");
 constexpr int64_t kSegNodes = kSegWaves * (64 * kSegC - 2 * kGroupHalo) + 2 * kGroupHalo;
 
 // AUTO picks the resident executor for FP32 storage on at most this many grids

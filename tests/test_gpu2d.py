@@ -213,6 +213,20 @@ def test_2d_in_place_steps_bitwise(G, mode, nx, ny, px, py, prec):
     assert rel(Xa, o["X"]) <= tol and max(errs(Fa, o)) <= 10 * tol
 
 
+def test_2d_allocates_what_fits_when_torch_has_no_room(G, monkeypatch):
+    """The Python handle without torch memory for its workspace."""
+    import torch
+    p = W.random_2d(np.random.default_rng(2), "tm", 90, 70)
+    with G.FdtdPlasma2D(p) as h:
+        X = h.run(30).spectra()
+
+    def full(*a, **kw):
+        raise torch.cuda.OutOfMemoryError("no room")
+    monkeypatch.setattr(G.torch, "empty", full)
+    with G.FdtdPlasma2D(p) as h:
+        assert h.workspace is None and np.array_equal(h.run(30).spectra(), X)
+
+
 def test_2d_step_composition_and_replay(G):
     p = W.random_2d(np.random.default_rng(5), "te", 70, 90)
     say("case 2d step composition")

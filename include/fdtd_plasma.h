@@ -69,8 +69,9 @@ enum { FDTD_SCHEME_CONSISTENT = 0, FDTD_SCHEME_PAPER_EQ13 = 1, FDTD_SCHEME_ETD1 
  *           halo recompute at the tile ends, ping-pong buffers (one-wave tiles:
  *           long runs of tiles are merged into spans of four waves, and CPML
  *           and role tiles, or all of a short problem, into segments);
- * RESIDENT: a launch per sample window; each workgroup keeps a whole grid in
- *           registers for the window (short grids, e.g. batches of slabs);
+ * RESIDENT: a launch per sample window; each workgroup keeps a whole grid, or
+ *           several short ones, in registers for the window (short grids, e.g.
+ *           batches of slabs);
  * MIXED:    per pass, the grids that fit a workgroup run as RESIDENT bins and
  *           the longer ones as TILED tiles (Mur or PEC ends; batches of
  *           uneven slabs);

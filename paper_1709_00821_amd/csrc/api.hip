@@ -614,6 +614,10 @@ bool build_bins(const fdtd_plasma_desc *d, Plan &p, bool skip_long = false)
 // fill the GPU) stays tiles, as do layers too thick for a segment's wave: with
 // the segments of 200 role tiles 4000 steps of a batch take 2.0 ms instead of 3.0, of
 // 700 3.5 instead of 3.9, of 1600 6.0 instead of 5.9 or (long slabs) 8.1 instead of 7.7.
+// CPML tiles, whose step is dearer, always become segments: 2048 steps FP64 of 100,
+// 1000 and 4096 grids of 500-3000 nodes 1.13, 3.05 and 12.0 ms instead of 2.32, 5.5 and
+// 15.7 (4096 of 100-500 nodes, which a tile holds whole, 8.5 instead of 8.0; 10.9 with
+// the branches the layers' step had).
 // Measured, a pass of 64 steps: the CPML tile of a 1.5 M-node grid took 53 us
 // and its role tiles 20, one after the other beside 45 us of bulk tiles, the
 // segments of both 19; the 4096-node paper setup 37 us a pass in three launches
@@ -717,9 +721,9 @@ void build_spans(const fdtd_plasma_desc *d, Plan &p, int c)
 
 // The longest grid up to which AUTO takes the resident executor in FP64 (the
 // executors give the same bits): grids that fit two nodes a lane, on a CU each.
-// 1000 nodes, 4096 steps: resident 0.99 ms, segments 1.12.  Above, a CU's four
-// SIMDs are the limit: 4096 nodes take 500 ns a step resident and 205 as
-// segments of several CUs.
+// 4096 steps: 1000 nodes resident 0.68 ms, as segments 0.82; 1500 nodes 0.75 either
+// way.  Above, a CU's four SIMDs are the limit: 2000 nodes 1.17 against 0.79, 4000
+// 1.63 against 0.83 as segments of several CUs.
 int64_t resident_auto64(const fdtd_plasma_desc *d)
 {
     return d->batch <= 256 ? kGroupShapes[0].nodes() : 0;
